@@ -135,6 +135,10 @@ struct SlotDev {
   int32_t nr;        // reorder interval N_R in steps (0: every rebuild reorders); a
                      // rebuild that does not reorder works like one under noreo
   int32_t nowin;     // MD_NO_WINDOW: no LDS window (every read from global memory)
+  double pk_scale;   // 2^16 / L: units of the packed positions
+  uint32_t pk_lim;   // largest squared packed distance of a pair within r_n (0: the
+                     // cell-layer rows have no room for packed positions)
+  int32_t pad1;
 };
 
 // Per-replica mutable control block.  Written by the host between launches,

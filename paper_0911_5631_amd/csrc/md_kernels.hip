@@ -434,6 +434,39 @@ __global__ void k_kick_end(Tables T) {
   C.clean = 0;
 }
 
+// Positions of the sorted atoms in 16 bits per coordinate (units of L / 2^16
+// from the box's lower corner; x and y in the low word, z in the high one's
+// low half), written by the sort for the traversal of the same step.  They
+// live in the cell-layer rows of set (k + 2) % 3, which nobody holds during
+// step k: the rows of state k are in set k % 3, those of state k + 1 (binned
+// ahead during step k) in set (k + 1) % 3.  SlotDev::pk_lim is 0 where the
+// rows are too few to hold them.
+typedef unsigned long long pk_t;
+typedef const __attribute__((address_space(1))) pk_t *gcpk;
+typedef short short2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ pk_t *pk_array(SlotC &S, int64_t k) {
+  return (pk_t *)S.H[(int)mod3(k + 2)];
+}
+__device__ __forceinline__ pk_t pk_of(SlotC &S, double x, double y, double z) {
+  const double q = S.pk_scale, h = S.halfL;
+  const uint32_t ux = (uint32_t)(int)((x + h) * q) & 0xffffu;
+  const uint32_t uy = (uint32_t)(int)((y + h) * q) & 0xffffu;
+  const uint32_t uz = (uint32_t)(int)((z + h) * q) & 0xffffu;
+  return ((pk_t)uz << 32) | (uy << 16) | ux;
+}
+// Squared distance of two packed positions; the 16-bit differences wrap, so
+// it is the distance of the nearest images.  Each coordinate is within one
+// unit of the true one, so a pair within r_n passes s <= (r_n + sqrt 3
+// units)^2 (SlotDev::pk_lim); the exact test follows for those that pass.
+__device__ __forceinline__ uint32_t pk_dist2(pk_t a, pk_t b) {
+  const short2v dxy = __builtin_bit_cast(short2v, (uint32_t)a) -
+                      __builtin_bit_cast(short2v, (uint32_t)b);
+  const short2v dz = __builtin_bit_cast(short2v, (uint32_t)(a >> 32)) -
+                     __builtin_bit_cast(short2v, (uint32_t)(b >> 32));
+  return (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(dxy, dxy, 0, false),
+                                          false);
+}
+
 // ---------------------------------------------------------------------------
 // (b): the counting sort by cell
 // ---------------------------------------------------------------------------
@@ -628,6 +661,8 @@ __global__ __launch_bounds__(TILE) void k_sort(Tables T, int s, int mode, int on
     const double L = S.L, halfL = S.halfL;
     const bool mixsp = S.nsp > 0;  // a mixture: the species move with the atoms
     const bool noreo = !reo;
+    const bool packed = S.pk_lim != 0;  // and their packed positions (near_rows)
+    const auto PK = gp(pk_array(S, k));
     auto move = [&](int a, int cc, int p) {
       if (p >= n || a < 0 || a >= n) return;  // inconsistent counts: never expected
       if (noreo) {
@@ -639,11 +674,14 @@ __global__ __launch_bounds__(TILE) void k_sort(Tables T, int s, int mode, int on
         for (int d = 0; d < 3; ++d) gp(S.P[pb][d])[a] = wrap1(gp(S.P[pb][d])[a], L, halfL);
         return;
       }
+      double x[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        gp(D.P[pb][d])[p] = wrap1(gp(S.P[pb][d])[a], L, halfL);
+        x[d] = wrap1(gp(S.P[pb][d])[a], L, halfL);
+        gp(D.P[pb][d])[p] = x[d];
         gp(D.V[vb][d])[p] = gp(S.V[vb][d])[a];
       }
+      if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
       gp(D.id)[p] = gp(S.id)[a];
       gp(D.cell)[p] = cc;
       if (mixsp) gp(D.sp)[p] = gp(S.sp)[a];
@@ -680,11 +718,14 @@ __global__ __launch_bounds__(TILE) void k_sort(Tables T, int s, int mode, int on
             for (int u4 = 0; u4 < 4; ++u4) {
               const int p = base + b + u4, a = v[b + u4];
               if (b + u4 >= cnt || p >= n || a < 0 || a >= n) continue;
+              double x[3];
 #pragma unroll
               for (int d = 0; d < 3; ++d) {
-                gp(D.P[pb][d])[p] = wrap1(pv[u4][d], L, halfL);
+                x[d] = wrap1(pv[u4][d], L, halfL);
+                gp(D.P[pb][d])[p] = x[d];
                 gp(D.V[vb][d])[p] = pv[u4][3 + d];
               }
+              if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
               gp(D.id)[p] = idv[u4];
               gp(D.cell)[p] = c;
               if (mixsp) gp(D.sp)[p] = spv[u4];
@@ -1145,9 +1186,11 @@ __device__ __forceinline__ void row_bounds(CSP CS, int G, int cx, int cy, int cz
   b[3] = CS[row + xe + 1];
 }
 
-// 27-cell traversal over the sorted atoms (offsets z-major, x fastest;
-// ascending storage index within a cell, which is ascending index before the
-// sort).  The three cells of an x-row are one contiguous range of storage
+// The general 27-cell traversal (offsets z-major, x fastest; ascending
+// storage index within a cell, which is ascending index before the sort):
+// atoms that are not stored in cell order, atoms whose list overflowed, and
+// systems without room for the packed positions (near_rows is the usual
+// traversal).  The three cells of an x-row are one contiguous range of storage
 // indices unless the row wraps, where it is two.  Candidates are read from
 // the LDS window (slot = storage index + the row piece's offset), or from
 // global memory for a piece the window could not hold.  Accepts r^2 < r_n^2
@@ -1181,175 +1224,121 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
   const bool whole = !global_only && w.whole, rows = !global_only && !whole && w.wt[0] >= 0;
   const int sr = rows ? ci / G - w.rf : 0;  // source row of the atom within the tile
   int m = 0;
-  // candidates j of [lo, hi); FROM_LDS: every lane of the wave reads the
-  // window (the usual case: one code path, the reads of four candidates in
-  // flight together), else each lane reads where its piece lives
   // without reordering, position j of cell order is the atom stored at perm[j]
   const bool noreo = unord;
   const gcint PERM = gp((const int32_t *)S.perm);
-  // SELF: the row holds atom i itself (the atom's own row, q = 4: the 27
-  // cells are distinct for G >= 3, so no other row does)
-  auto candidates = [&](auto from_lds, auto self, int lo, int hi, int delta, uint32_t code,
-                        double bx, double by, double bz) {
-    // ALL_LDS also means that no lane of the wave applies an image shift
-    constexpr bool ALL_LDS = decltype(from_lds)::value, SELF = decltype(self)::value;
-    const bool lds = ALL_LDS || delta != NOSLOT;
-    for (int j0 = lo; j0 < hi; j0 += 4) {
-      double xj[4], yj[4], zj[4];
-      int sj[4], js[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        // from the window, a candidate past hi reads one of the (padded)
-        // slots after the range's last, and is not taken
-        const int j = ALL_LDS ? j0 + u : min(j0 + u, hi - 1);
-        js[u] = j;
-        if (ALL_LDS || lds) {
-          xj[u] = sx[j + delta];
-          yj[u] = sy[j + delta];
-          zj[u] = sz[j + delta];
-          if (MIX) sj[u] = ssp[j + delta];
-        } else {
-          if (noreo) js[u] = PERM[j];
-          xj[u] = X[js[u]];
-          yj[u] = Y[js[u]];
-          zj[u] = Z[js[u]];
-          if (MIX) sj[u] = SP[js[u]];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        if (j >= hi || (SELF && js[u] == i)) continue;
-        double dx = xi - xj[u], dy = yi - yj[u], dz = zi - zj[u];
-        if (!ALL_LDS) {
-          dx = dx + bx;
-          dy = dy + by;
-          dz = dz + bz;
-        }
-        const double s = (dx * dx + dy * dy) + dz * dz;
-        if (s < rn2) {
-          if (build) {
-            const uint32_t idx = lds ? (uint32_t)(j + delta) : ((uint32_t)js[u] | GFLAG);
-            *wp = (int32_t)(idx | code);
-            ++m;
-            wp += m < mcap ? np : (size_t)0;
-          }
-          if (MIX) {
-            const int kk = (spi * MAXSP + sj[u]) & (MAXSP * MAXSP - 1);
-            if (force && s < tab->rc2[kk]) pair_accum_mix<R>(a, dx, dy, dz, s, tab, kk, energy);
-          } else if (force && s < rc2) {
-            pair_accum<R>(a, dx, dy, dz, s, ushift, energy);
-          }
-        }
-      }
-    }
-  };
-  auto range = [&](bool own, int lo, int hi, int delta, uint32_t code, double bx, double by,
-                   double bz) {
-    if (__ballot(lo < hi && (delta == NOSLOT || code != 0)) != 0)
-      candidates(std::false_type{}, std::true_type{}, lo, hi, delta, code, bx, by, bz);
-    else if (own)
-      candidates(std::true_type{}, std::true_type{}, lo, hi, delta, code, bx, by, bz);
-    else
-      candidates(std::true_type{}, std::false_type{}, lo, hi, delta, code, bx, by, bz);
-  };
-  // storage bounds of row q: the x-neighbours that do not wrap (one
-  // contiguous range) and the one wrapped cell, visited first when cx == 0
-  // (cell G-1) and last when cx == G-1 (cell 0).  The bounds of the next row
-  // are loaded before the current one is visited, so their latency is hidden
-  // behind it.
-  const int xm0 = max(cx - 1, 0), xm1 = min(cx + 2, G);
-  const int xe = cx == 0 ? G - 1 : 0;
+  // A lane at an x-edge of the box (cx = 0 or G-1) has two ranges per row,
+  // the wrapped cell and the row's own cells: it visits both in x order (cell
+  // G-1 first when cx = 0, cell 0 last when cx = G-1), each candidate with
+  // its own window offset and x image shift.
   const bool wlo = cx == 0, whi = cx == G - 1 && cx != 0;
-  auto bounds = [&](int q, int (&b)[4]) { row_bounds(CS, G, cx, cy, cz, q, b); };
-  // A wave with lanes at an x-edge of the box (cx = 0 or G-1) visits each
-  // row as one loop over the lane's two ranges, the wrapped cell and the
-  // row's own cells in x order (cell G-1 first when cx = 0, cell 0 last
-  // when cx = G-1: the order of separate visits, so the same list and the
-  // same sums), instead of three loops of which two run for a few lanes.
-  // Every candidate then takes its own window offset and x image shift.
   const bool edge = wlo || whi;
   const bool anyedge = __ballot(edge) != 0;
-  // ALL_LDS: every piece of the row is in the window for every lane; YZ:
-  // some lane's row is a y or z image; SELF: the atom's own row
-  auto merged_t = [&](auto all_lds, auto yz, auto self, int loM, int hiM, int dM, int loW,
-                      int hiW, int dW, uint32_t cyz, double by, double bz) {
-    constexpr bool ALL_LDS = decltype(all_lds)::value, YZ = decltype(yz)::value,
-                   SELF = decltype(self)::value;
-    const int loF = wlo ? loW : loM, hiF = wlo ? hiW : hiM;
-    const int loS = wlo ? loM : loW, hiS = wlo ? hiM : hiW;
-    const int lenF = hiF - loF, tot = lenF + (hiS - loS);
+  // One row, in two passes over at most 32 candidates at a time: the first
+  // only tests (r^2 < r_n^2, one acceptance bit per candidate and lane), the
+  // second takes each lane's accepted candidates in order, lists them and
+  // adds their forces.  EDGE: some lane has two ranges.  own: the row may hold
+  // atom i itself (the 27 cells are distinct for G >= 3, so only q = 4 does).
+  auto row = [&](auto edg, bool own, int loM, int hiM, int dM, int loW, int hiW, int dW,
+                 uint32_t cyz, double by, double bz) {
+    constexpr bool EDGE = decltype(edg)::value;
+    // candidate k: k < lenF of the first range, then the second
+    int loF = loM, lenF = hiM - loM, tot = lenF, loS = 0;
+    if (EDGE) {
+      const int lenW = edge ? hiW - loW : 0;
+      lenF = wlo ? lenW : tot;
+      loF = wlo ? loW : loM;
+      loS = (wlo ? loM : loW) - lenF;
+      tot += lenW;
+    }
     const double bw = wlo ? L : -L;
     const uint32_t cw = cyz | ((wlo ? 1u : 3u) << J_BITS);
-    for (int k0 = 0; k0 < tot; k0 += 4) {
-      double xj[4], yj[4], zj[4];
-      int sj[4], js[4], jj[4];
-      bool isw[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = min(k0 + u, tot - 1);
+    // position j in cell order, window offset and whether the x image applies
+    auto where = [&](int k, int &j, int &d, bool &isw) {
+      isw = false;
+      j = loF + k;
+      d = dM;
+      if (EDGE) {
         const bool inF = k < lenF;
-        const int j = inF ? loF + k : loS + (k - lenF);
-        isw[u] = edge && inF == wlo;
-        const int d = isw[u] ? dW : dM;
-        jj[u] = j;
-        js[u] = j;
-        if (ALL_LDS || d != NOSLOT) {
-          xj[u] = sx[j + d];
-          yj[u] = sy[j + d];
-          zj[u] = sz[j + d];
-          if (MIX) sj[u] = ssp[j + d];
-        } else {
-          if (noreo) js[u] = PERM[j];
-          xj[u] = X[js[u]];
-          yj[u] = Y[js[u]];
-          zj[u] = Z[js[u]];
-          if (MIX) sj[u] = SP[js[u]];
+        j = (inF ? loF : loS) + k;
+        isw = edge && inF == wlo;
+        d = isw ? dW : dM;
+      }
+    };
+    auto coords = [&](int j, int d, double &x, double &y, double &z, int &js, int &sj) {
+      js = j;
+      if (d != NOSLOT) {
+        x = sx[j + d];
+        y = sy[j + d];
+        z = sz[j + d];
+        if (MIX) sj = ssp[j + d];
+      } else {
+        if (noreo) js = PERM[j];
+        x = X[js];
+        y = Y[js];
+        z = Z[js];
+        if (MIX) sj = SP[js];
+      }
+    };
+    auto separation = [&](double x, double y, double z, bool isw, double &dx, double &dy,
+                          double &dz) {
+      dx = xi - x;
+      dy = yi - y;
+      dz = zi - z;
+      if (EDGE) dx = dx + (isw ? bw : 0.0);
+      dy = dy + by;
+      dz = dz + bz;
+      return (dx * dx + dy * dy) + dz * dz;
+    };
+    for (int c0 = 0; __ballot(c0 < tot) != 0; c0 += 32) {
+      const int end = min(tot - c0, 32);
+      uint32_t acc = 0;
+      int g = 0;
+      for (; g < end; g += 4) {
+        double x[4], y[4], z[4];
+        bool isw[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = min(c0 + g + u, tot - 1);  // (past the last: cleared below)
+          int j, d, js, sj;
+          where(k, j, d, isw[u]);
+          coords(j, d, x[u], y[u], z[u], js, sj);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          double dx, dy, dz;
+          acc = (acc << 1) | (separation(x[u], y[u], z[u], isw[u], dx, dy, dz) < rn2 ? 1u : 0u);
         }
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (k0 + u >= tot || (SELF && js[u] == i)) continue;
-        double dx = xi - xj[u], dy = yi - yj[u], dz = zi - zj[u];
-        dx = dx + (isw[u] ? bw : 0.0);
-        if (YZ) {
-          dy = dy + by;
-          dz = dz + bz;
+      // candidate c0 in the highest bit, those past the last cleared
+      acc = end > 0 ? (acc >> (g - end)) << (32 - end) : 0u;
+      while (acc != 0) {
+        const int b = __clz((int)acc);
+        acc &= ~(0x80000000u >> b);
+        int j, d, js, sj;
+        bool isw;
+        double x, y, z, dx, dy, dz;
+        where(c0 + b, j, d, isw);
+        coords(j, d, x, y, z, js, sj);
+        if (own && js == i) continue;
+        const double s = separation(x, y, z, isw, dx, dy, dz);
+        if (build) {
+          const uint32_t idx =
+              d != NOSLOT ? (uint32_t)(j + d) : ((uint32_t)js | GFLAG);
+          *wp = (int32_t)(idx | (isw ? cw : cyz));
+          ++m;
+          wp += m < mcap ? np : (size_t)0;
         }
-        const double s = (dx * dx + dy * dy) + dz * dz;
-        if (s < rn2) {
-          if (build) {
-            const int d = isw[u] ? dW : dM;
-            const uint32_t idx =
-                ALL_LDS || d != NOSLOT ? (uint32_t)(jj[u] + d) : ((uint32_t)js[u] | GFLAG);
-            *wp = (int32_t)(idx | (isw[u] ? cw : cyz));
-            ++m;
-            wp += m < mcap ? np : (size_t)0;
-          }
-          if (MIX) {
-            const int kk = (spi * MAXSP + sj[u]) & (MAXSP * MAXSP - 1);
-            if (force && s < tab->rc2[kk]) pair_accum_mix<R>(a, dx, dy, dz, s, tab, kk, energy);
-          } else if (force && s < rc2) {
-            pair_accum<R>(a, dx, dy, dz, s, ushift, energy);
-          }
+        if (MIX) {
+          const int kk = (spi * MAXSP + sj) & (MAXSP * MAXSP - 1);
+          if (force && s < tab->rc2[kk]) pair_accum_mix<R>(a, dx, dy, dz, s, tab, kk, energy);
+        } else if (force && s < rc2) {
+          pair_accum<R>(a, dx, dy, dz, s, ushift, energy);
         }
       }
     }
   };
-  // the usual row (interior, wholly in the window, not the atom's own) skips
-  // the per-candidate choice of window or global memory, the y/z image
-  // shifts (zero there: x + 0 == x) and the test for atom i itself
-  auto merged = [&](bool own, int loM, int hiM, int dM, int loW, int hiW, int dW, uint32_t cyz,
-                    double by, double bz) {
-    if (!edge) loW = hiW = 0;
-    const bool glob = (hiM > loM && dM == NOSLOT) || (hiW > loW && dW == NOSLOT);
-    if (own || __ballot(glob || by != 0.0 || bz != 0.0) != 0)
-      merged_t(std::false_type{}, std::true_type{}, std::true_type{}, loM, hiM, dM, loW, hiW, dW,
-               cyz, by, bz);
-    else
-      merged_t(std::true_type{}, std::false_type{}, std::false_type{}, loM, hiM, dM, loW, hiW,
-               dW, cyz, by, bz);
-  };
+  auto bounds = [&](int q, int (&b)[4]) { row_bounds(CS, G, cx, cy, cz, q, b); };
   // (row 0's bounds may have been loaded by the caller, ahead of the window)
   int cur[4], nxt[4];
   if (pre0) {
@@ -1375,14 +1364,160 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
       d0 = w.dl[e + 1];
       dg = w.dl[e + 2];
     }
+    const int dw = wlo ? dg : d0;
     if (anyedge)
-      merged(q == 4, cur[0], cur[1], dm, cur[2], cur[3], wlo ? dg : d0, cyz, by, bz);
+      row(std::true_type{}, q == 4, cur[0], cur[1], dm, cur[2], cur[3], dw, cyz, by, bz);
     else
-      range(q == 4, cur[0], cur[1], dm, cyz, 0.0, by, bz);
+      row(std::false_type{}, q == 4, cur[0], cur[1], dm, 0, 0, 0, cyz, by, bz);
 #pragma unroll
     for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
   }
   return m;
+}
+
+// 27-cell traversal over the sorted atoms, first half (offsets z-major, x
+// fastest; ascending storage index within a cell, which is ascending index
+// before the sort): emit(entry) for every candidate whose packed position is
+// near enough to atom i's, in order, entry being its list entry (window slot
+// of its row piece, or storage index with GFLAG; image code).  The three
+// cells of an x-row are one contiguous range of storage indices unless the
+// row wraps (a lane at an x-edge of the box), where it is two, taken in x
+// order.
+// What bounds a rebuild step is VALU issue and the waits of its dependent
+// chains: the full test is 9 FP64 operations on three 8-byte coordinates, a
+// wave runs ~135 of them per lane for the ~77 candidates a lane has, and the
+// accept path (list store, pair arithmetic) ran for every candidate that any
+// lane accepted.  Packed, a candidate is one 8-byte load, four operations and
+// a compare, without image shifts or a choice of where its piece lives; the
+// exact test runs for the ~12 per lane that pass, together with the pair
+// arithmetic, over the finished list.  Evaluation with a build, N = 256 000:
+// 63.0 -> 54.5 us, VALU instructions per wave 6 143 -> 4 325; the FP64 cell
+// method at N = 2 048 41.5 -> 35.0 us per step.
+// EDGE: some lane of the wave is at an x-edge of the box; the other waves skip
+// the choice between the two ranges.
+template <bool EDGE, class Emit>
+__device__ __forceinline__ void near_rows(SlotC &S, int i, int ci, const Window &w, const pk_t *pk,
+                                          const int (&pre0)[4], Emit &&emit) {
+  const int G = S.G;
+  const uint32_t lim = S.pk_lim;
+  // 32-bit byte offsets from uniform bases
+  typedef const __attribute__((address_space(1))) char *gcchar;
+  const gcchar CS = (gcchar)gp((const int32_t *)S.cs), PK = (gcchar)gp(pk);
+  auto cs_at = [&](int c) { return *(gcint)(CS + (uint32_t)(4 * c)); };
+  const int cx = ci % G, cy = (ci / G) % G, cz = ci / (G * G);
+  const bool whole = w.whole, rows = !whole && w.wt[0] >= 0;
+  const int sr = rows ? ci / G - w.rf : 0;  // source row of the atom within the tile
+  const pk_t me = *(gcpk)(PK + (uint32_t)(8 * i));
+  // a lane at an x-edge visits the wrapped cell first when cx = 0 (cell G-1),
+  // last when cx = G-1 (cell 0)
+  const bool wlo = EDGE && cx == 0, edge = EDGE && (cx == 0 || cx == G - 1);
+  const uint32_t cxw = (wlo ? 1u : 3u) << J_BITS;
+  const int xm0 = max(cx - 1, 0), xm1 = min(cx + 2, G), xe = cx == 0 ? G - 1 : 0;
+  // the cells of a row start at plane + yrow[dy + 1]
+  int yrow[3];
+  uint32_t ycode[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    yrow[d] = wrap_cell(cy + d - 1, G, &ycode[d]) * G;
+    ycode[d] <<= J_BITS + 2;
+  }
+  uint32_t zc;
+  int plane = wrap_cell(cz - 1, G, &zc) * G * G;
+  int cur[4], nxt[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int u = 0; u < 4; ++u) cur[u] = pre0[u];
+#pragma unroll 1
+  for (int pz = 0; pz < 3; ++pz) {
+    const uint32_t zcode = zc << (J_BITS + 4);
+    const int next_plane = wrap_cell(cz + pz, G, &zc) * G * G;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      // the next row's bounds are loaded before this one is visited
+      if (d < 2 || pz < 2) {
+        const int row = d < 2 ? plane + yrow[d < 2 ? d + 1 : 0] : next_plane + yrow[0];
+        nxt[0] = cs_at(row + xm0);
+        nxt[1] = cs_at(row + xm1);
+        if (EDGE) {
+          nxt[2] = cs_at(row + xe);
+          nxt[3] = cs_at(row + xe + 1);
+        }
+      }
+      const uint32_t cyz = ycode[d] | zcode;
+      int dm = NOSLOT, dw = NOSLOT;
+      if (whole) {
+        dm = dw = 0;
+      } else if (rows) {
+        const int e = 3 * (sr * 9 + 3 * pz + d);
+        dm = w.dl[e];
+        if (EDGE) dw = w.dl[e + (wlo ? 2 : 1)];
+      }
+      // candidates k = 0 .. tot-1: the first range (k < lenF), then the
+      // second; candidate k of a range is atom lo + k, its entry e + k
+      int loF = cur[0], lenF = cur[1] - cur[0], tot = lenF, loS = 0;
+      uint32_t eF = (dm == NOSLOT ? (uint32_t)cur[0] | GFLAG : (uint32_t)(cur[0] + dm)) | cyz,
+               eS = 0;
+      int self = pz == 1 && d == 1 ? i - cur[0] : -1;
+      if (EDGE) {
+        const int lenM = lenF, lenW = edge ? cur[3] - cur[2] : 0;
+        const uint32_t eM = eF, eW = (dw == NOSLOT ? (uint32_t)cur[2] | GFLAG
+                                                   : (uint32_t)(cur[2] + dw)) | cyz | cxw;
+        tot += lenW;
+        lenF = wlo ? lenW : lenM;
+        loF = wlo ? cur[2] : cur[0];
+        loS = (wlo ? cur[0] : cur[2]) - lenF;
+        eF = wlo ? eW : eM;
+        eS = (wlo ? eM : eW) - (uint32_t)lenF;
+        if (self >= 0 && wlo) self += lenW;
+      }
+      for (int c0 = 0; __ballot(c0 < tot) != 0; c0 += 32) {
+        // one bit per candidate c0 .. c0+31, the first in the highest (a
+        // group of four may read up to three past its range: the array has
+        // the room, and their bits are dropped)
+        auto test = [&](int lo, int k, int end) {
+          uint32_t acc = 0;
+          const int cnt = end - k;
+          uint32_t off = 8u * (uint32_t)(lo + k);
+          for (int g = 0; g < cnt; g += 4, off += 32) {
+            pk_t c[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = *(gcpk)(PK + off + 8 * u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              acc = (acc << 1) | (pk_dist2(me, c[u]) <= lim ? 1u : 0u);
+          }
+          return cnt > 0 ? acc >> (-cnt & 3) : 0u;
+        };
+        const int end = min(tot, c0 + 32);
+        uint32_t acc = test(loF, c0, EDGE ? min(lenF, end) : end);
+        if (EDGE) {
+          const int k2 = max(lenF, c0);
+          const uint32_t acc2 = test(loS, k2, end);
+          if (k2 < end) acc = (acc << ((end - k2) & 31)) | acc2;  // (32 only after none)
+        }
+        if (end <= c0) continue;
+        // candidate c0 + b in bit b
+        acc = __brev(acc << (32 - (end - c0)));
+        if (pz == 1 && d == 1 && self >= c0 && self < c0 + 32) acc &= ~(1u << (self - c0));
+        while (acc != 0) {
+          const int k = c0 + __ffs((int)acc) - 1;
+          acc &= acc - 1;
+          emit((EDGE && k >= lenF ? eS : eF) + (uint32_t)k);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+    }
+    plane = next_plane;
+  }
+}
+template <class Emit>
+__device__ __forceinline__ void near_atoms(SlotC &S, int i, int ci, const Window &w,
+                                           const pk_t *pk, const int (&pre0)[4], Emit &&emit) {
+  const int cx = ci % S.G;
+  if (__ballot(cx == 0 || cx == S.G - 1) != 0)
+    near_rows<true>(S, i, ci, w, pk, pre0, emit);
+  else
+    near_rows<false>(S, i, ci, w, pk, pre0, emit);
 }
 
 // Coordinates of neighbour-list entry e: from the LDS window, or from
@@ -1542,6 +1677,22 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
     if (threadIdx.x < WSTRIDE) win.wt[threadIdx.x] = wtv;
     __syncthreads();
   }
+  // a cell step over atoms in cell order: which candidates are near comes from
+  // their packed positions, while the window's loads are in flight
+  const bool near = cells && S.pk_lim != 0 && !unordered(S, *cview(&C), k, mode);
+  if (cells) stage_window<MIX>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
+  int mr = 0;
+  if (near && build && act) {
+    // the list with its few entries that are only nearly near; an atom with
+    // more than mcap of them (its list may overflow) is done again below
+    const int mcap = S.mcap;
+    auto wp = gp(S.W) + i;
+    near_atoms(S, i, ci, win, pk_array(S, k), b0, [&](uint32_t e1) {
+      *wp = (int32_t)e1;
+      ++mr;
+      wp += mr < mcap ? np : (size_t)0;
+    });
+  }
   // The first NP entries that live outside the window: their coordinates
   // are gathered now, while the window is staged, instead of inside the
   // pair loop (by the waves that have such entries; only a group holding
@@ -1566,14 +1717,76 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
       }
     }
   }
-  if (cells || list) {
-    stage_window<MIX>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
-    __syncthreads();
-  }
+  if (list) stage_window<MIX>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
+  if (cells || list) __syncthreads();
 
   Acc<R> a{(R)0, (R)0, (R)0, (R)0, (R)0};
   if (act) {
-    if (cells) {
+    if (near && (!build || mr <= S.mcap)) {
+      // exact test, force, and the list closed up over the entries that fail
+      const double rn2 = S.rn2, rc2 = S.rc2;
+      const R ushift = (R)S.ushift;
+      const bool energy = mode != MODE_STEP || last || ACC;
+      auto pair = [&](uint32_t e1, double xj, double yj, double zj, int sj) {
+        // each 2-bit field sign-extended is the multiple of L (exact products)
+        const double dx = xi - xj + (double)((int32_t)(e1 << (32 - J_BITS - 2)) >> 30) * L;
+        const double dy = yi - yj + (double)((int32_t)(e1 << (32 - J_BITS - 4)) >> 30) * L;
+        const double dz = zi - zj + (double)((int32_t)e1 >> 30) * L;
+        const double s2 = (dx * dx + dy * dy) + dz * dz;
+        if (!(s2 < rn2)) return false;
+        if (MIX) {
+          const int kk = (spi * MAXSP + sj) & (MAXSP * MAXSP - 1);
+          if (force && s2 < tab->rc2[kk]) pair_accum_mix<R>(a, dx, dy, dz, s2, tab, kk, energy);
+        } else if (force && s2 < rc2) {
+          pair_accum<R>(a, dx, dy, dz, s2, ushift, energy);
+        }
+        return true;
+      };
+      if (build) {
+        const auto Wb = gp(S.W) + i;
+        uint32_t en[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) en[u] = u < mr ? (uint32_t)Wb[(size_t)u * np] : 0u;
+        for (int q = 0; __ballot(q < mr) != 0; q += 4) {
+          uint32_t eg[4];
+          double xj[4], yj[4], zj[4];
+          int sj[4] = {0, 0, 0, 0};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) eg[u] = en[u];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            en[u] = q + 4 + u < mr ? (uint32_t)Wb[(size_t)(q + 4 + u) * np] : 0u;
+          if (__ballot((((eg[0] | eg[1]) | (eg[2] | eg[3])) & GFLAG) != 0) == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const uint32_t sl = eg[u] & IDX_MASK;
+              xj[u] = sx[sl];
+              yj[u] = sy[sl];
+              zj[u] = sz[sl];
+              if (MIX) sj[u] = ssp[sl];
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              entry_pos<MIX>(eg[u], X, Y, Z, sx, sy, sz, xj[u], yj[u], zj[u], SP, ssp, sj[u]);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (q + u < mr && pair(eg[u], xj[u], yj[u], zj[u], sj[u])) {
+              if (m != q + u) Wb[(size_t)m * np] = (int32_t)eg[u];
+              ++m;
+            }
+        }
+        gp(S.m)[i] = m;
+      } else {
+        near_atoms(S, i, ci, win, pk_array(S, k), b0, [&](uint32_t e1) {
+          double xj, yj, zj;
+          int sj = 0;
+          entry_pos<MIX>(e1, X, Y, Z, sx, sy, sz, xj, yj, zj, SP, ssp, sj);
+          (void)pair(e1, xj, yj, zj, sj);
+        });
+      }
+    } else if (cells) {
       m = traverse_sorted<R, MIX>(S, i, ci, X, Y, Z, win, sx, sy, sz, xi, yi, zi, build, force,
                                   mode != MODE_STEP || last || ACC, a, ssp, SP, spi, tab,
                                   unordered(S, *cview(&C), k, mode), false, b0);
