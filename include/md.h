@@ -254,8 +254,10 @@ md_status md_build_nebr(md_system *s);
 md_status md_forces(md_system *s);
 
 /* Advance n_steps leapfrog steps (a)-(e), rebuilding on the device whenever
- * the displacement rule fires.  Work is replayed from captured HIP graphs.
- * Async. */
+ * the displacement rule fires.  A system of up to about 262 000 atoms takes
+ * many steps per launch; a larger one, or one whose launches md_configure
+ * gave grids or a sort split of their own, replays captured HIP graphs.  The
+ * trajectory is the same bit for bit.  Async. */
 md_status md_step(md_system *s, int64_t n_steps);
 
 /* Properties after the last completed step (or creation / md_forces).

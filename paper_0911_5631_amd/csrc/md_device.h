@@ -73,6 +73,7 @@ enum : int32_t {
   ERR_NONFINITE = 8,  // NaN / Inf coordinate
   ERR_UNBINNED = 16,  // the rule fired at a step whose positions were not binned
                       // ahead (repairable: the host bins them and resumes)
+  ERR_STALL = 32,     // a barrier of k_run gave up (never expected)
 };
 
 // Binning ahead (see bins_due): r(k) is binned during step k-1 when the
@@ -164,7 +165,7 @@ struct CtlDev {
   int32_t bin_ring[3]; // 1 if step k bins r(k+1) (decided by k_sort of step k), slot k % 3
   int32_t err;         // latched ERR_* bits
   int32_t max_h;       // largest cell occupancy seen by a sort
-  int32_t pad1;
+  int32_t late_bins;   // rebuilds of k_run whose positions were not binned ahead
   // properties reduced by k_props
   double ke, pe, vir, vmax2;
   int64_t sum_m;
@@ -179,6 +180,7 @@ enum { HDR_NTILES = 0, HDR_NCTILES = 1, HDR_SPLIT = 2, HDR_ORDER = 3 };
 // kernel's workgroups (ORDER_PASSES or ORDER_SLABS, see TileWalk)
 enum { ORDER_PASSES = 0, ORDER_SLABS = 1 };
 constexpr size_t WALK_BYTES = 16 * 64 * 4;  // Tables::walk
+constexpr size_t RUN_BYTES = 88 * 64 * 4;   // Tables::run
 
 // Each replica has two descriptors (see SlotDev); CtlDev::var_ring says
 // which one holds a given state.
@@ -192,6 +194,7 @@ struct Tables {
   // group x (x = block & 7), walk[64 (8 + x)] its workgroups that finished;
   // zero between launches (the group's last workgroup resets both)
   int32_t *walk;
+  int32_t *run;               // k_run's roll call and barriers (zero between launches)
   int32_t nslots;
 };
 

@@ -48,6 +48,7 @@ namespace {
 constexpr int MIN_DEFAULT_MCAP = 48;
 constexpr int MIN_DEFAULT_HCAP = 16;
 constexpr int GRAPH_CHUNK = 64;      // steps per replay graph (largest)
+constexpr int RUN_STEPS = 256;       // steps per launch of k_run
 constexpr int PROFILE_SETS = 2;      // ping-pong event sets when profiling
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -202,6 +203,9 @@ struct Engine {
   CtlDev *d_ctl = nullptr;
   int32_t *d_tile_rep = nullptr, *d_ctile_rep = nullptr, *d_hdr = nullptr;
   int32_t *d_walk = nullptr;    // k_step's tile claims (Tables::walk)
+  int32_t *d_run = nullptr;     // k_run's roll call and barriers (Tables::run)
+  int cus = 0;
+  int run_cap[2][2][2] = {};    // k_run's workgroups resident at once, + 1 (0: not asked yet)
   int tile_cap = 0, ctile_cap = 0;
   CtlDev *h_ctl = nullptr;      // pinned
   SlotDev *h_slots = nullptr;   // pinned [2 * max_slots]
@@ -241,6 +245,7 @@ struct Engine {
     t.ctile_rep = d_ctile_rep;
     t.hdr = d_hdr;
     t.walk = d_walk;
+    t.run = d_run;
     t.nslots = max_slots;
     return t;
   }
@@ -335,8 +340,10 @@ md_status engine_init(Engine *e, int max_slots, const md_allocator *a, void *str
   if (hipGetDevice(&dev) == hipSuccess) e->device = dev;
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-      cus > 0)
+      cus > 0) {
     e->resident = 4 * cus;
+    e->cus = cus;
+  }
   hipError_t err = hipStreamCreateWithFlags(&e->work, hipStreamNonBlocking);
   if (err == hipSuccess) err = hipEventCreateWithFlags(&e->ev_in, hipEventDisableTiming);
   if (err == hipSuccess) err = hipEventCreateWithFlags(&e->ev_out, hipEventDisableTiming);
@@ -348,7 +355,8 @@ md_status engine_init(Engine *e, int max_slots, const md_allocator *a, void *str
   e->d_ctl = (CtlDev *)e->dmalloc(sizeof(CtlDev) * max_slots);
   e->d_hdr = (int32_t *)e->dmalloc(256);
   e->d_walk = (int32_t *)e->dmalloc(WALK_BYTES);
-  if (!e->d_slots || !e->d_ctl || !e->d_hdr || !e->d_walk) return MD_ERR_OOM;
+  e->d_run = (int32_t *)e->dmalloc(RUN_BYTES);
+  if (!e->d_slots || !e->d_ctl || !e->d_hdr || !e->d_walk || !e->d_run) return MD_ERR_OOM;
   err = hipHostMalloc((void **)&e->h_ctl, sizeof(CtlDev) * max_slots, hipHostMallocDefault);
   if (err == hipSuccess)
     err = hipHostMalloc((void **)&e->h_slots, sizeof(SlotDev) * 2 * max_slots,
@@ -360,6 +368,7 @@ md_status engine_init(Engine *e, int max_slots, const md_allocator *a, void *str
   if (err == hipSuccess) err = hipMemsetAsync(e->d_slots, 0, sizeof(SlotDev) * 2 * max_slots, e->work);
   if (err == hipSuccess) err = hipMemsetAsync(e->d_hdr, 0, 256, e->work);
   if (err == hipSuccess) err = hipMemsetAsync(e->d_walk, 0, WALK_BYTES, e->work);
+  if (err == hipSuccess) err = hipMemsetAsync(e->d_run, 0, RUN_BYTES, e->work);
   if (err == hipSuccess) err = hipStreamSynchronize(e->work);
   return err == hipSuccess ? MD_OK : e->fail("engine init", err);
 }
@@ -383,6 +392,7 @@ void engine_free(Engine *e) {
   e->dfree(e->d_ctl);
   e->dfree(e->d_hdr);
   e->dfree(e->d_walk);
+  e->dfree(e->d_run);
   e->dfree(e->d_tile_rep);
   e->dfree(e->d_ctile_rep);
   if (e->h_ctl) (void)hipHostFree(e->h_ctl);
@@ -609,6 +619,7 @@ md_status status_of(int err) {
   if (err & ERR_ESCAPED) return MD_ERR_ATOM_ESCAPED;
   if (err & ERR_CELL) return MD_ERR_CELL_OVERFLOW;
   if (err & ERR_UNBINNED) return MD_ERR_STATE;  // repaired by settle(); never expected here
+  if (err & ERR_STALL) return MD_ERR_HIP;       // never expected
   return MD_OK;
 }
 
@@ -772,6 +783,7 @@ md_status repair_cells(Engine *e, int s) {
   if ((err = clear_sets(e, r)) != hipSuccess) return e->fail("regrow", err);
   c.err &= ~ERR_CELL;
   c.err_step = INT64_MAX;
+  if (!c.clean) c.bins_step = c.done + 1;  // (the held r(done + 1) is binned below)
   md_status st = upload_tables(e);
   if (st == MD_OK) st = write_ctl(e, s);
   if (st != MD_OK) return st;
@@ -833,6 +845,27 @@ hipGraphExec_t step_graph(Engine *e, int k) {
   return x;
 }
 
+// Workgroups of a k_run launch: one per tile, a multiple of 8 (each XCD has an
+// eighth of the tiles).
+int run_grid(const Engine *e) { return (e->rep[0]->g.ntiles + 7) / 8 * 8; }
+
+// Whether the steps of this engine are taken by k_run, several per launch: a
+// single system whose tiles are all resident at once (1 024 tiles, 262 144
+// atoms; a mixture 768), unless its launches are timed one by one or were
+// given grids of their own.  At N = 256 000 (1 000 tiles) a step takes 26.6 us
+// this way and 30.7 in two launches, at N = 864 12.2 and 16.7; beyond the limit
+// each workgroup would walk several tiles with device-scope reads, where
+// k_step's tiles share their neighbours through the XCD's L2.
+bool use_run(Engine *e) {
+  if (e->batch || e->profiling || !e->rep[0] || e->cus <= 0) return false;
+  if (e->grid_req > 0 || e->cgrid_req > 0 || e->split_req > 0) return false;
+  if (e->prec != PREC_FP32 && e->prec != PREC_FP64) return false;
+  const bool acc = e->accum || e->trace;
+  int &cap = e->run_cap[e->prec == PREC_FP64][acc][e->mix];
+  if (cap == 0) cap = 1 + run_capacity(e->prec, acc, e->mix, e->cus);
+  return run_grid(e) < cap;
+}
+
 md_status prof_collect(Engine *e, int set) {
   const int k = e->prof_pending[set];
   if (!k) return MD_OK;
@@ -852,6 +885,7 @@ md_status prof_collect(Engine *e, int set) {
 // steps_per_run and its repeated halvings, plain kernels), so that no
 // md_step pays for a capture.
 md_status prepare_graphs(Engine *e) {
+  if (use_run(e)) return MD_OK;
   for (int k = e->steps_per_run; k >= 1; k >>= 1)
     if (!step_graph(e, k)) return MD_ERR_HIP;
   hipError_t err = hipStreamSynchronize(e->work);
@@ -885,10 +919,26 @@ md_status replay(Engine *e, int k) {
   return err == hipSuccess ? MD_OK : e->fail("graph launch", err);
 }
 
-// Advance a single system from absolute step `from` to `to` in replays of
-// steps_per_run steps and a halving decomposition of the rest.
+// Advance a single system from absolute step `from` to `to` in launches of
+// up to steps_per_run steps (k_run), or in replays of steps_per_run steps and
+// a halving decomposition of the rest.
 md_status run_steps(Engine *e, int64_t from, int64_t to) {
   int64_t pos = from;
+  if (use_run(e)) {
+    const Tables T = e->tables();
+    while (pos < to) {
+      const int k = (int)std::min<int64_t>(e->trace ? MAX_REPLAY : RUN_STEPS, to - pos);
+      const hipError_t err = launch_run(T, run_grid(e), k, to, !e->trace, e->prec,
+                                        e->accum || e->trace, e->mix, e->work);
+      if (err != hipSuccess) return e->fail("run launch", err);
+      if (e->trace) {
+        launch_trace(T, k, e->work);
+        launch_replay_end(T, k, e->work);
+      }
+      pos += k;
+    }
+    return e->check("run launches");
+  }
   while (pos < to) {
     int k = e->steps_per_run;
     while (k > to - pos) k >>= 1;
@@ -997,7 +1047,7 @@ void fill_props(const Replica *r, const CtlDev &c, md_props_t *o) {
   o->max_nebr = c.max_m;
   o->max_cell = c.max_h;
   o->cells_per_edge = r->g.G;
-  o->n_late_bins = r->late_bins;
+  o->n_late_bins = r->late_bins + c.late_bins;
   // displacement accumulated through the held step and the rule's decision
   // for the next one (the step kernel recomputes the same from the rings)
   if (!r->g.cell_only && c.clean) {
@@ -1444,10 +1494,12 @@ md_status md_step(md_system *s, int64_t n_steps) {
   if ((st = v.enter()) != MD_OK) return st;
   const int64_t from = e->host_target;
   const int64_t to = from + n_steps;
-  Tables T = e->tables();
-  launch_set_target(T, 0, to, e->work);
-  launch_kick(T, e->grid, e->work);
-  if ((st = e->check("kick")) != MD_OK) return st;
+  if (!use_run(e)) {  // (k_run sets the target and kicks by itself)
+    Tables T = e->tables();
+    launch_set_target(T, 0, to, e->work);
+    launch_kick(T, e->grid, e->work);
+    if ((st = e->check("kick")) != MD_OK) return st;
+  }
   if ((st = run_steps(e, from, to)) != MD_OK) return st;
   e->host_target = to;
   return v.leave();
@@ -1504,6 +1556,7 @@ md_status md_set_state(md_system *s, const double *pos, const double *vel) {
   const int64_t step = c.clean ? c.done : c.done + 1;
   const int variant = held_variant(c);
   e->accum = false;  // an open block ends without a result
+  r->late_bins += c.late_bins;
   if ((st = upload_state(e, r, variant, step, pos, vel)) != MD_OK) return st;
   if (r->mixbuf && (st = upload_species(e, r, variant)) != MD_OK) return st;
   reset_ctl(c, step, variant, c.n_rebuilds, c.max_h);

@@ -49,6 +49,51 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gp(T *p) {
 typedef const __attribute__((address_space(1))) double *gcdouble;
 typedef const __attribute__((address_space(1))) int32_t *gcint;
 
+// The thread's index, worked out here and not before: what depends on it only
+// (lane masks, offsets) would otherwise be hoisted out of the loops over tiles
+// and steps, held across them and spilled.
+__device__ __forceinline__ int tid_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  __builtin_assume(t >= 0 && t < TILE);
+  return t;
+}
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ bool uniform(bool b) {
+  return __builtin_amdgcn_readfirstlane(b ? 1 : 0) != 0;
+}
+__device__ __forceinline__ double uniform(double v) {
+  const long long b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Loads and stores of data that other workgroups of the same launch write or
+// read (k_run; COH): device-scope, so they neither stay in nor come from an
+// XCD's own L2.  In the other kernels a launch only reads what earlier
+// launches wrote, and they are plain.
+template <bool COH, class T>
+__device__ __forceinline__ T ld(const __attribute__((address_space(1))) T *p) {
+  if constexpr (COH) return __hip_atomic_load((const T *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return *p;
+}
+template <bool COH, class T>
+__device__ __forceinline__ void st(__attribute__((address_space(1))) T *p, T v) {
+  if constexpr (COH)
+    __hip_atomic_store((T *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+
 // Replica descriptors are written by the host only, between launches: read
 // through the constant address space their fields are scalar loads held in
 // SGPRs (a wave-uniform descriptor) instead of vector loads into VGPRs.
@@ -391,6 +436,28 @@ __device__ __forceinline__ bool rebuild_rule(const SlotC &S, int64_t force_step,
 // ---------------------------------------------------------------------------
 // (a): first half kick and drift of a clean replica, and binning of r(k+1)
 // ---------------------------------------------------------------------------
+// One tile of a clean replica at state k; bin: r(k+1) into its set.
+template <bool COH>
+__device__ __forceinline__ void kick_tile(SlotC &S, CtlDev &C, int lt, int64_t k, bool bin) {
+  const int i = lt * TILE + threadIdx.x;
+  if (i >= S.n) return;
+  const int pb = (int)(k & 1), vb = (int)((k + 1) & 1);
+  double f[3];
+  for (int a = 0; a < 3; ++a)
+    f[a] = S.fp64 ? gp((const double *)S.F)[a * S.npad + i]
+                  : (double)gp((const float *)S.F)[a * S.npad + i];
+  double xn[3];
+  for (int a = 0; a < 3; ++a) {
+    const double v = gp(S.V[vb][a])[i] + S.hdt * f[a];
+    gp(S.V[vb][a])[i] = v;
+    xn[a] = gp(S.P[pb][a])[i] + S.dt * v;
+    st<COH>(&gp(S.P[pb ^ 1][a])[i], xn[a]);
+  }
+  if (bin)
+    bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
+  else
+    check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+}
 __global__ __launch_bounds__(TILE) void k_kick(Tables T) {
   const int nt = T.hdr[HDR_NTILES];
   for (int t = xcd_block(blockIdx.x, gridDim.x); t < nt; t += gridDim.x) {
@@ -402,24 +469,7 @@ __global__ __launch_bounds__(TILE) void k_kick(Tables T) {
     if ((C.err != 0 && C.err_step <= C.done) || !C.clean || C.done >= C.target) continue;
     const int64_t k = C.done;
     const bool bin = bins_due(slot(T, 2 * r), C, k + 1);
-    const int i = (t - S.tile_off) * TILE + threadIdx.x;
-    if (i >= S.n) continue;
-    const int pb = (int)(k & 1), vb = (int)((k + 1) & 1);
-    double f[3];
-    for (int a = 0; a < 3; ++a)
-      f[a] = S.fp64 ? gp((const double *)S.F)[a * S.npad + i]
-                    : (double)gp((const float *)S.F)[a * S.npad + i];
-    double xn[3];
-    for (int a = 0; a < 3; ++a) {
-      const double v = gp(S.V[vb][a])[i] + S.hdt * f[a];
-      gp(S.V[vb][a])[i] = v;
-      xn[a] = gp(S.P[pb][a])[i] + S.dt * v;
-      gp(S.P[pb ^ 1][a])[i] = xn[a];
-    }
-    if (bin)
-      bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
-    else
-      check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+    kick_tile<false>(S, C, t - S.tile_off, k, bin);
   }
 }
 
@@ -470,6 +520,226 @@ __device__ __forceinline__ uint32_t pk_dist2(pk_t a, pk_t b) {
 // ---------------------------------------------------------------------------
 // (b): the counting sort by cell
 // ---------------------------------------------------------------------------
+// Positions listed at a time, and the LDS of the sort.
+constexpr int SORT_CAP = 1024;
+struct SortLds {
+  int s_red[4], s_wsum[4], s_bsum[4], s_any[4];
+  int s_bc[TILE], s_bb[TILE], s_bp[TILE];
+  int src[SORT_CAP];
+  uint8_t lc[SORT_CAP];
+};
+// The atoms in replica rep's tiles before tile upto, kept by a workgroup from
+// one of its units to the next.
+struct SortRun {
+  int rep = -1, upto = 0, pre = 0;
+};
+
+// Share sp of nsp of cell tile t of replica r at step k (the sorts of a step:
+// mode MODE_STEP, v(k-1/2) is carried; of the held state: v(k)): from
+// descriptor S into D, or in place without reordering (!reo).
+__device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t k, int mode,
+                                          bool reo, int t, int sp, int nsp, int r, SortRun &run,
+                                          SortLds &lds) {
+  const int tid = tid_here();
+  const int set = (int)mod3(k);
+  const int pb = (int)(k & 1);
+  const int vb = mode == MODE_STEP ? pb : pb ^ 1;
+  const int lt = t - S.ctile_off;
+  const int w = tid >> 6, l = tid & 63;
+
+  // atoms in the earlier tiles: a workgroup takes its units in increasing
+  // order, so the sum kept from its previous unit of the same replica only
+  // grows by the tiles in between (about the grid's size; O(tiles) loads
+  // per workgroup instead of every earlier tile at every unit).  Eight
+  // loads in flight per thread: integer sums, so the grouping does not
+  // change the result.
+  const auto TC = gp((const int32_t *)S.tcnt[set]);
+  if (run.rep != r || run.upto > lt) {
+    run.rep = r;
+    run.upto = 0;
+    run.pre = 0;
+  }
+  int pre = 0;
+  {
+    int q = run.upto + (int)tid;
+    for (; q + 7 * TILE < lt; q += 8 * TILE) {
+      int p8[8];
+#pragma unroll
+      for (int u8 = 0; u8 < 8; ++u8) p8[u8] = TC[q + u8 * TILE];
+#pragma unroll
+      for (int u8 = 0; u8 < 8; ++u8) pre += p8[u8];
+    }
+    for (; q < lt; q += TILE) pre += TC[q];
+  }
+  for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
+  if (l == 0) lds.s_red[w] = pre;
+
+  // workgroup exclusive scan of one cell count per thread
+  const int c = lt * CTILE + tid;
+  const int cnt = c < S.ncell ? gp(S.cnt[set])[c] : 0;
+  int incl = cnt;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(incl, o, 64);
+    if (l >= o) incl += y;
+  }
+  if (l == 63) lds.s_wsum[w] = incl;
+  const int wmax = wave_max_i(cnt);
+  __syncthreads();
+  run.pre += ((lds.s_red[0] + lds.s_red[1]) + lds.s_red[2]) + lds.s_red[3];
+  run.upto = lt;
+  int before = run.pre;
+  for (int q = 0; q < w; ++q) before += lds.s_wsum[q];
+  const int base = before + incl - cnt;
+  if (sp == 0) {
+    if (l == 0 && wmax > C.max_h) atomicMax(&C.max_h, wmax);
+    if (c <= S.ncell) gp(S.cs)[c] = base;  // c == ncell: the total, n
+  }
+
+  // Every atom goes to base of its cell + its rank by current index.  This
+  // share takes the tile's positions [s0, s1) in cell order, SORT_CAP at a
+  // time: first the storage index of the atom that belongs at each is listed
+  // in LDS, then the atoms are moved, consecutive threads to consecutive
+  // positions, so the stores are whole lines and all of a thread's loads are
+  // in flight together.  (Moved by the thread that holds their cell, four at
+  // a time, every store instruction wrote 8 bytes to each of 64 cells: sorting
+  // took 176 us at 4 x 10^6, now 134.)
+  const int n = S.n;
+  const double L = S.L, halfL = S.halfL;
+  const bool mixsp = S.nsp > 0;  // a mixture: the species move with the atoms
+  const bool packed = S.pk_lim != 0;  // and their packed positions (near_rows)
+  const auto PK = gp(pk_array(S, k));
+  const int base0 = run.pre;
+  const int total = ((lds.s_wsum[0] + lds.s_wsum[1]) + lds.s_wsum[2]) + lds.s_wsum[3];
+  const int s1 = base0 + (int)((int64_t)total * (sp + 1) / nsp);
+  const bool big = c < S.ncell && cnt > 8 && cnt <= min(S.hcap, 8191);
+  for (int s0 = base0 + (int)((int64_t)total * sp / nsp); s0 < s1; s0 += SORT_CAP) {
+    const int se = min(s1, s0 + SORT_CAP);
+    auto list = [&](int p, int atom, int lc) {
+      if (p < s0 || p >= se) return;
+      lds.src[p - s0] = atom;
+      lds.lc[p - s0] = (uint8_t)lc;
+    };
+    const bool here = c < S.ncell && cnt > 0 && base < se && base + cnt > s0;
+    // cells of up to eight atoms (the usual ones): a sorting network
+    if (here && !big) {
+      if (cnt <= 8 && cnt <= S.hcap) {
+        const int32_t *row = S.H[set] + (size_t)c * S.hcap;
+        int v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < cnt ? gp(row)[e] : INT_MAX;
+        sort8(v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e < cnt) list(base + e, v[e], tid);
+      } else {
+        // a cell that spilled into the overflow list: repeated minimum searches
+        visit_cell(S, set, c, cnt, [&](int atom, int q) { list(base + q, atom, tid); });
+      }
+    }
+    // larger cells whose members all sit in their rows, by the whole
+    // workgroup: their atoms are listed (big cell j holds entries s_bp[j] ...
+    // of the list), and each atom's rank is the number of smaller indices in
+    // its row
+    const bool bigh = here && big;
+    const bool anybig = __ballot(bigh) != 0;
+    if (l == 0) lds.s_any[w] = anybig ? 1 : 0;
+    __syncthreads();
+    if ((lds.s_any[0] | lds.s_any[1]) | (lds.s_any[2] | lds.s_any[3])) {
+      const int bv = bigh ? ((1 << 21) | cnt) : 0;  // (cell count, atom count)
+      int binc = bv;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(binc, o, 64);
+        if (l >= o) binc += y;
+      }
+      if (l == 63) lds.s_bsum[w] = binc;
+      __syncthreads();
+      int bbefore = 0;
+      for (int q = 0; q < w; ++q) bbefore += lds.s_bsum[q];
+      const int bex = bbefore + binc - bv;
+      if (bigh) {
+        const int j = bex >> 21;
+        lds.s_bc[j] = c;
+        lds.s_bb[j] = base;
+        lds.s_bp[j] = bex & ((1 << 21) - 1);
+      }
+      const int btot = ((lds.s_bsum[0] + lds.s_bsum[1]) + lds.s_bsum[2]) + lds.s_bsum[3];
+      const int nb = btot >> 21, B = btot & ((1 << 21) - 1);
+      __syncthreads();
+      for (int q = tid; q < B; q += TILE) {
+        int lo = 0, hi = nb - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (lds.s_bp[mid] <= q) lo = mid;
+          else hi = mid - 1;
+        }
+        const int cj = lds.s_bc[lo];
+        const int cntj = (lo + 1 < nb ? lds.s_bp[lo + 1] : B) - lds.s_bp[lo];
+        const auto row = gp((const int32_t *)S.H[set]) + (size_t)cj * S.hcap;
+        const int v = row[q - lds.s_bp[lo]];
+        int rank = 0;
+        for (int f = 0; f < cntj; ++f) rank += row[f] < v ? 1 : 0;
+        list(lds.s_bb[lo] + rank, v, cj - lt * CTILE);
+      }
+      __syncthreads();
+    }
+    for (int p0 = s0 + tid; p0 < se; p0 += 4 * TILE) {
+      int at[4], cc[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int p = p0 + u * TILE;
+        at[u] = p < se ? lds.src[p - s0] : -1;
+        cc[u] = p < se ? lt * CTILE + lds.lc[p - s0] : 0;
+        if (p >= n || at[u] >= n) at[u] = -1;  // inconsistent counts: never expected
+      }
+      if (!reo) {
+        // no reordering: position p of cell order refers to the atom where it
+        // is; it is wrapped in place (read and written by this thread only)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = at[u];
+          if (q < 0) continue;
+          gp(S.perm)[p0 + u * TILE] = q;
+          gp(S.cell)[q] = cc[u];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) gp(S.P[pb][d])[q] = wrap1(gp(S.P[pb][d])[q], L, halfL);
+        }
+        continue;
+      }
+      double pv[4][6];
+      int idv[4], spv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = max(at[u], 0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          pv[u][d] = gp(S.P[pb][d])[q];
+          pv[u][3 + d] = gp(S.V[vb][d])[q];
+        }
+        idv[u] = gp(S.id)[q];
+        spv[u] = mixsp ? gp(S.sp)[q] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (at[u] < 0) continue;
+        const int p = p0 + u * TILE;
+        double x[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          x[d] = wrap1(pv[u][d], L, halfL);
+          gp(D.P[pb][d])[p] = x[d];
+          gp(D.V[vb][d])[p] = pv[u][3 + d];
+        }
+        if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
+        gp(D.id)[p] = idv[u];
+        gp(D.cell)[p] = cc[u];
+        if (mixsp) gp(D.sp)[p] = spv[u];
+      }
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+}
+
 // Workgroup t of a replica takes cell tile t (CTILE cells, one per thread):
 // cell_start of the tile's first cell is the sum of the occupancies of the
 // earlier tiles (counted while binning), cell_start of its cells follows
@@ -482,19 +752,15 @@ __device__ __forceinline__ uint32_t pk_dist2(pk_t a, pk_t b) {
 //   does not fire leave; v(k-1/2) is carried.
 //   otherwise: the held clean state (k = done); v(k) is carried; k_flip
 //   switches the variant afterwards.
-__global__ __launch_bounds__(TILE) void k_sort(Tables T, int s, int mode, int only) {
-  __shared__ int s_red[4];
-  __shared__ int s_wsum[4];
-  __shared__ int s_bsum[4];
-  __shared__ int s_bc[TILE], s_bb[TILE], s_bp[TILE];
+__global__ __launch_bounds__(TILE, 4) void k_sort(Tables T, int s, int mode, int only) {
+  __shared__ SortLds lds;
   // the decision for a replica is launch-invariant: a workgroup works it out
   // once for a run of consecutive cell tiles of one replica
   int rc = -1, var = 0;
   int64_t k = 0;
   bool skip = true, rebuild = false, unbinned = false, reo = true;
   double d1 = 0.0;
-  // the atoms in a replica's tiles before tile run_upto (see below)
-  int run_rep = -1, run_upto = 0, run_pre = 0;
+  SortRun run;
   // one replica: every unit is replica 0's
   const bool solo = T.nslots == 1;
   // last reordering before step k, and whether step k bins r(k+1) (MODE_STEP)
@@ -600,187 +866,8 @@ __global__ __launch_bounds__(TILE) void k_sort(Tables T, int s, int mode, int on
         continue;
       }
     }
-    SlotC &S = slot(T, 2 * r + var);
-    SlotC &D = slot(T, 2 * r + (var ^ 1));
-    const int set = (int)mod3(k);
-    const int pb = (int)(k & 1);
-    const int vb = mode == MODE_STEP ? pb : pb ^ 1;
-    const int lt = t - S.ctile_off;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-
-    // atoms in the earlier tiles: a workgroup takes its units in increasing
-    // order, so the sum kept from its previous unit of the same replica only
-    // grows by the tiles in between (about the grid's size; O(tiles) loads
-    // per workgroup instead of every earlier tile at every unit).  Eight
-    // loads in flight per thread: integer sums, so the grouping does not
-    // change the result.
-    const auto TC = gp((const int32_t *)S.tcnt[set]);
-    if (run_rep != r || run_upto > lt) {
-      run_rep = r;
-      run_upto = 0;
-      run_pre = 0;
-    }
-    int pre = 0;
-    {
-      int q = run_upto + (int)threadIdx.x;
-      for (; q + 7 * TILE < lt; q += 8 * TILE) {
-        int p8[8];
-#pragma unroll
-        for (int u8 = 0; u8 < 8; ++u8) p8[u8] = TC[q + u8 * TILE];
-#pragma unroll
-        for (int u8 = 0; u8 < 8; ++u8) pre += p8[u8];
-      }
-      for (; q < lt; q += TILE) pre += TC[q];
-    }
-    for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
-    if (l == 0) s_red[w] = pre;
-
-    // workgroup exclusive scan of one cell count per thread
-    const int c = lt * CTILE + threadIdx.x;
-    const int cnt = c < S.ncell ? gp(S.cnt[set])[c] : 0;
-    int incl = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o, 64);
-      if (l >= o) incl += y;
-    }
-    if (l == 63) s_wsum[w] = incl;
-    const int wmax = wave_max_i(cnt);
-    __syncthreads();
-    run_pre += ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
-    run_upto = lt;
-    int before = run_pre;
-    for (int q = 0; q < w; ++q) before += s_wsum[q];
-    const int base = before + incl - cnt;
-    if (sp == 0) {
-      if (l == 0 && wmax > C.max_h) atomicMax(&C.max_h, wmax);
-      if (c <= S.ncell) gp(S.cs)[c] = base;  // c == ncell: the total, n
-    }
-
-    // every atom goes to base of its cell + its rank by current index
-    const int n = S.n;
-    const double L = S.L, halfL = S.halfL;
-    const bool mixsp = S.nsp > 0;  // a mixture: the species move with the atoms
-    const bool noreo = !reo;
-    const bool packed = S.pk_lim != 0;  // and their packed positions (near_rows)
-    const auto PK = gp(pk_array(S, k));
-    auto move = [&](int a, int cc, int p) {
-      if (p >= n || a < 0 || a >= n) return;  // inconsistent counts: never expected
-      if (noreo) {
-        // no reordering: position p of cell order refers to the atom where
-        // it is; it is wrapped in place (read and written by this thread only)
-        gp(S.perm)[p] = a;
-        gp(S.cell)[a] = cc;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) gp(S.P[pb][d])[a] = wrap1(gp(S.P[pb][d])[a], L, halfL);
-        return;
-      }
-      double x[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        x[d] = wrap1(gp(S.P[pb][d])[a], L, halfL);
-        gp(D.P[pb][d])[p] = x[d];
-        gp(D.V[vb][d])[p] = gp(S.V[vb][d])[a];
-      }
-      if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
-      gp(D.id)[p] = gp(S.id)[a];
-      gp(D.cell)[p] = cc;
-      if (mixsp) gp(D.sp)[p] = gp(S.sp)[a];
-    };
-    // cells of up to eight atoms (the usual ones) by the thread that holds
-    // them: a sorting network, then moves four at a time with every load of
-    // a batch issued before its stores; with shares, thread i of share i %
-    // nsp
-    const bool big = c < S.ncell && cnt > 8 && cnt <= min(S.hcap, 8191);
-    if (c < S.ncell && cnt > 0 && !big && threadIdx.x % nsp == sp) {
-      if (cnt <= 8 && cnt <= S.hcap && !noreo) {
-        const int32_t *row = S.H[set] + (size_t)c * S.hcap;
-        int v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = e < cnt ? gp(row)[e] : INT_MAX;
-        sort8(v);
-#pragma unroll
-        for (int b = 0; b < 8; b += 4) {
-          if (b < cnt) {
-            double pv[4][6];
-            int idv[4], spv[4];
-#pragma unroll
-            for (int u4 = 0; u4 < 4; ++u4) {
-              const int a = min(max(b + u4 < cnt ? v[b + u4] : v[0], 0), n - 1);
-#pragma unroll
-              for (int d = 0; d < 3; ++d) {
-                pv[u4][d] = gp(S.P[pb][d])[a];
-                pv[u4][3 + d] = gp(S.V[vb][d])[a];
-              }
-              idv[u4] = gp(S.id)[a];
-              spv[u4] = mixsp ? gp(S.sp)[a] : 0;
-            }
-#pragma unroll
-            for (int u4 = 0; u4 < 4; ++u4) {
-              const int p = base + b + u4, a = v[b + u4];
-              if (b + u4 >= cnt || p >= n || a < 0 || a >= n) continue;
-              double x[3];
-#pragma unroll
-              for (int d = 0; d < 3; ++d) {
-                x[d] = wrap1(pv[u4][d], L, halfL);
-                gp(D.P[pb][d])[p] = x[d];
-                gp(D.V[vb][d])[p] = pv[u4][3 + d];
-              }
-              if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
-              gp(D.id)[p] = idv[u4];
-              gp(D.cell)[p] = c;
-              if (mixsp) gp(D.sp)[p] = spv[u4];
-            }
-          }
-        }
-      } else {
-        // a cell that spilled into the overflow list (repeated minimum
-        // searches), and every cell without reordering
-        visit_cell(S, set, c, cnt, [&](int a, int q) { move(a, c, base + q); });
-      }
-    }
-    // larger cells whose members all sit in their rows, by the whole
-    // workgroup: their atoms are listed (big cell j holds entries
-    // s_bp[j] ... of the list), this share takes its slice, and each atom's
-    // rank is the number of smaller indices in its row
-    if (__syncthreads_or(big)) {
-      const int bv = big ? ((1 << 21) | cnt) : 0;  // (cell count, atom count)
-      int binc = bv;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(binc, o, 64);
-        if (l >= o) binc += y;
-      }
-      if (l == 63) s_bsum[w] = binc;
-      __syncthreads();
-      int bbefore = 0;
-      for (int q = 0; q < w; ++q) bbefore += s_bsum[q];
-      const int bex = bbefore + binc - bv;
-      if (big) {
-        const int j = bex >> 21;
-        s_bc[j] = c;
-        s_bb[j] = base;
-        s_bp[j] = bex & ((1 << 21) - 1);
-      }
-      const int btot = ((s_bsum[0] + s_bsum[1]) + s_bsum[2]) + s_bsum[3];
-      const int nb = btot >> 21, B = btot & ((1 << 21) - 1);
-      __syncthreads();
-      const int a0 = (int)((int64_t)B * sp / nsp), a1 = (int)((int64_t)B * (sp + 1) / nsp);
-      for (int a = a0 + (int)threadIdx.x; a < a1; a += TILE) {
-        int lo = 0, hi = nb - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_bp[mid] <= a) lo = mid;
-          else hi = mid - 1;
-        }
-        const int cj = s_bc[lo];
-        const int cntj = (lo + 1 < nb ? s_bp[lo + 1] : B) - s_bp[lo];
-        const auto row = gp((const int32_t *)S.H[set]) + (size_t)cj * S.hcap;
-        const int v = row[a - s_bp[lo]];
-        int rank = 0;
-        for (int f = 0; f < cntj; ++f) rank += row[f] < v ? 1 : 0;
-        move(v, cj, s_bb[lo] + rank);
-      }
-    }
-    __syncthreads();
+    sort_unit(slot(T, 2 * r + var), slot(T, 2 * r + (var ^ 1)), C, k, mode, reo, t, sp, nsp, r,
+              run, lds);
   }
 }
 
@@ -905,15 +992,16 @@ struct Window {
 // not, pieces stay in global memory), merging storage-adjacent ones into
 // staging intervals, with wave prefix sums.  The staging table also goes to
 // S.win for the list steps until the next sort.
-__device__ void make_window(SlotC &S, int lt, Window &w, int *scratch) {
+__device__ __forceinline__ void make_window(SlotC &S, int lt, Window &w, int *scratch) {
+  const int tid = tid_here();
   __shared__ int s_np;
   int *piece = scratch;              // [2 * 192] start, end
   int *pdelta = scratch + 2 * 192;   // [192] slot - storage index, or NOSLOT
   const int n = S.n;
-  const int lane = threadIdx.x;
+  const int lane = tid;
   int T = INT_MAX, xa = 0, xb = 0, ell = 0, pos = 0, np = 0;
   bool full = false, w0 = false, wg = false;
-  if (threadIdx.x < 64) {
+  if (tid < 64) {
     const int G = S.G;
     const int i_f = lt * TILE, i_l = min(n, i_f + TILE) - 1;
     const auto CL = gp((const int32_t *)S.cell);
@@ -1027,7 +1115,7 @@ __device__ void make_window(SlotC &S, int lt, Window &w, int *scratch) {
     }
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
+  if (tid < 64) {
     const int npc = s_np;
     if (npc == -2) {
       if (lane == 0) {
@@ -1107,7 +1195,7 @@ __device__ void make_window(SlotC &S, int lt, Window &w, int *scratch) {
     }
   }
   __syncthreads();
-  if (threadIdx.x < 64 && T != INT_MAX) {
+  if (tid < 64 && T != INT_MAX) {
     const int dm = pdelta[pos + (w0 ? 1 : 0)];
     w.dl[3 * ell] = dm;
     w.dl[3 * ell + 1] = full ? dm : (w0 ? pdelta[pos] : NOSLOT);
@@ -1116,16 +1204,31 @@ __device__ void make_window(SlotC &S, int lt, Window &w, int *scratch) {
   // the staging table for the list steps until the next sort
   auto WG = gp(S.win) + (size_t)lt * WSTRIDE;
   const int nint = w.wt[0];
-  if ((int)threadIdx.x < 1 + 3 * max(nint, 0)) WG[threadIdx.x] = w.wt[threadIdx.x];
+  if ((int)tid < 1 + 3 * max(nint, 0)) WG[tid] = w.wt[tid];
   __syncthreads();
+}
+
+__device__ __forceinline__ void stage_species(const int *wt, gcint SP, int8_t *ssp) {
+  const int tid = tid_here(), nint = wt[0];
+  if (nint <= 0) return;
+  const int total = wt[3 * nint] + wt[3 * nint - 1];
+  int q = 0, end = wt[2];
+  for (int sl = tid; sl < total; sl += TILE) {
+    while (sl >= end) {
+      ++q;
+      end = wt[3 * q + 3] + wt[3 * q + 2];
+    }
+    ssp[sl] = (int8_t)SP[wt[3 * q + 1] + (sl - wt[3 * q + 3])];
+  }
 }
 
 // Stage the window's atoms (positions of the current step) into LDS.
 // MIX: the species of the window's atoms go to ssp beside the coordinates.
-template <bool MIX>
+template <bool MIX, bool COH>
 __device__ __forceinline__ void stage_window(const int *wt, gcdouble X, gcdouble Y, gcdouble Z,
                                              double *sx, double *sy, double *sz, gcint SP,
                                              int8_t *ssp) {
+  const int tid = tid_here();
   // The intervals fill slots 0 .. total-1 in order.  The coordinates go
   // straight from global memory into LDS (loads that write LDS, not
   // registers): wave w fills chunks of 32 slots c = w, w + 4, ..., lane l
@@ -1135,11 +1238,12 @@ __device__ __forceinline__ void stage_window(const int *wt, gcdouble X, gcdouble
   // after the staging waits for them.
   const int nint = wt[0];
   if (nint <= 0) return;
+  constexpr int AUX = COH ? 16 : 0;  // 16: device scope (sc1), see ld<COH>
   const int total = wt[3 * nint] + wt[3 * nint - 1];
   typedef __attribute__((address_space(1))) const char *gcchar;
   typedef __attribute__((address_space(3))) void *lvoid;
-  const int l = threadIdx.x & 63;
-  const int c0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int l = tid & 63;
+  const int c0 = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const int nch = (total + 31) >> 5;
   int q = 0, end = wt[2];
   for (int c = c0; c < nch; c += TILE / 64) {
@@ -1150,23 +1254,14 @@ __device__ __forceinline__ void stage_window(const int *wt, gcdouble X, gcdouble
         end = wt[3 * q + 3] + wt[3 * q + 2];
       }
       const size_t off = (size_t)(wt[3 * q + 1] + (sl - wt[3 * q + 3])) * 8 + 4 * (l & 1);
-      __builtin_amdgcn_global_load_lds((gcchar)X + off, (lvoid)((char *)sx + 256 * c), 4, 0, 0);
-      __builtin_amdgcn_global_load_lds((gcchar)Y + off, (lvoid)((char *)sy + 256 * c), 4, 0, 0);
-      __builtin_amdgcn_global_load_lds((gcchar)Z + off, (lvoid)((char *)sz + 256 * c), 4, 0, 0);
+      __builtin_amdgcn_global_load_lds((gcchar)X + off, (lvoid)((char *)sx + 256 * c), 4, 0, AUX);
+      __builtin_amdgcn_global_load_lds((gcchar)Y + off, (lvoid)((char *)sy + 256 * c), 4, 0, AUX);
+      __builtin_amdgcn_global_load_lds((gcchar)Z + off, (lvoid)((char *)sz + 256 * c), 4, 0, AUX);
     }
   }
-  if constexpr (MIX) {
-    // the species bytes through registers (after the coordinates' loads
-    // have gone out)
-    int qs = 0, es = wt[2];
-    for (int sl = threadIdx.x; sl < total; sl += TILE) {
-      while (sl >= es) {
-        ++qs;
-        es = wt[3 * qs + 3] + wt[3 * qs + 2];
-      }
-      ssp[sl] = (int8_t)SP[wt[3 * qs + 1] + (sl - wt[3 * qs + 3])];
-    }
-  }
+  // the species bytes through registers (after the coordinates' loads have
+  // gone out)
+  if constexpr (MIX) stage_species(wt, SP, ssp);
 }
 
 // Storage bounds of neighbour row q (dz = q / 3 - 1, dy = q % 3 - 1) of an
@@ -1199,7 +1294,7 @@ __device__ __forceinline__ void row_bounds(CSP CS, int G, int cx, int cy, int cz
 // by the sort, so they are read as stored.
 // MIX: a mixture; the candidates' species come from ssp (LDS) or SP, atom
 // i's is spi, and each pair takes its own cutoff and parameters from tab.
-template <typename R, bool MIX>
+template <typename R, bool MIX, bool COH>
 __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble X,
                                                gcdouble Y, gcdouble Z, const Window &w,
                                                const double *sx, const double *sy,
@@ -1217,7 +1312,7 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
   // list overflows keeps overwriting its last row; its list is not used)
   auto wp = gp(S.W) + i;
   const size_t np = (size_t)S.npad;
-  const auto CS = cview((const int32_t *)S.cs);  // written by the sort, read-only here
+  const auto CS = gp((const int32_t *)S.cs);
   const int cx = ci % G, cy = (ci / G) % G, cz = ci / (G * G);
   // global_only: candidates from global memory (the window's row table is
   // not at hand)
@@ -1274,9 +1369,9 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
         if (MIX) sj = ssp[j + d];
       } else {
         if (noreo) js = PERM[j];
-        x = X[js];
-        y = Y[js];
-        z = Z[js];
+        x = ld<COH>(&X[js]);
+        y = ld<COH>(&Y[js]);
+        z = ld<COH>(&Z[js]);
         if (MIX) sj = SP[js];
       }
     };
@@ -1522,16 +1617,16 @@ __device__ __forceinline__ void near_atoms(SlotC &S, int i, int ci, const Window
 
 // Coordinates of neighbour-list entry e: from the LDS window, or from
 // global memory when the entry carries a storage index.
-template <bool MIX>
+template <bool MIX, bool COH>
 __device__ __forceinline__ void entry_pos(uint32_t e, gcdouble X, gcdouble Y, gcdouble Z,
                                           const double *sx, const double *sy, const double *sz,
                                           double &xj, double &yj, double &zj, gcint SP,
                                           const int8_t *ssp, int &sj) {
   const uint32_t idx = e & IDX_MASK;
   if (e & GFLAG) {
-    xj = X[idx];
-    yj = Y[idx];
-    zj = Z[idx];
+    xj = ld<COH>(&X[idx]);
+    yj = ld<COH>(&Y[idx]);
+    zj = ld<COH>(&Z[idx]);
     if (MIX) sj = SP[idx];
   } else {
     xj = sx[idx];
@@ -1566,6 +1661,74 @@ __device__ __forceinline__ void list_pair(Acc<R> &a, bool ok, uint32_t e, double
   }
 }
 
+// Four entries q0 .. q0+3 of an atom's list of m (their coordinate reads
+// together).  A group without image codes anywhere in the wave skips the
+// shifts.
+// PRE: they are among the first NP, whose coordinates outside the window have
+// been gathered into g*.
+struct Four {
+  uint32_t e[4];
+};
+template <typename R, bool MIX, bool COH, bool PRE, int NP>
+__device__ __forceinline__ void list_group(Acc<R> &a, int q0, int m, Four f, gcdouble X,
+                                           gcdouble Y, gcdouble Z, const double *sx,
+                                           const double *sy, const double *sz, double xi, double yi,
+                                           double zi, double L, double rc2, R ushift, bool energy,
+                                           const PairTab *tab, int spi, gcint SP,
+                                           const int8_t *ssp, const double *gx, const double *gy,
+                                           const double *gz, const int *gs) {
+  bool ok[4];
+  uint32_t eg[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    ok[u] = q0 + u < m;
+    eg[u] = ok[u] ? f.e[u] : 0u;
+  }
+  const uint32_t any = (eg[0] | eg[1]) | (eg[2] | eg[3]);
+  double xj[4], yj[4], zj[4];
+  int sj[4] = {0, 0, 0, 0};
+  if (__ballot((any & GFLAG) != 0) == 0) {
+    // the usual case: every entry of the wave is a window slot
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t sl = eg[u] & IDX_MASK;
+      xj[u] = sx[sl];
+      yj[u] = sy[sl];
+      zj[u] = sz[sl];
+      if (MIX) sj[u] = ssp[sl];
+    }
+  } else if constexpr (PRE) {
+    // window slots from LDS (slot 0 for an entry outside it), the others from
+    // the gathered coordinates
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool g = (eg[u] & GFLAG) != 0;
+      const uint32_t sl = g ? 0u : eg[u] & IDX_MASK;
+      const int qu = q0 + u < NP ? q0 + u : NP - 1;
+      xj[u] = g ? gx[qu] : sx[sl];
+      yj[u] = g ? gy[qu] : sy[sl];
+      zj[u] = g ? gz[qu] : sz[sl];
+      if (MIX) sj[u] = g ? gs[qu] : ssp[sl];
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      entry_pos<MIX, COH>(eg[u], X, Y, Z, sx, sy, sz, xj[u], yj[u], zj[u], SP, ssp, sj[u]);
+  }
+  auto kk = [&](int u) { return (spi * MAXSP + sj[u]) & (MAXSP * MAXSP - 1); };
+  if (__ballot((any >> J_BITS) != 0) == 0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      list_pair<R, false, MIX>(a, ok[u], eg[u], xi, yi, zi, xj[u], yj[u], zj[u], L, rc2, ushift,
+                               energy, kk(u), tab);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      list_pair<R, true, MIX>(a, ok[u], eg[u], xi, yi, zi, xj[u], yj[u], zj[u], L, rc2, ushift,
+                              energy, kk(u), tab);
+  }
+}
+
 // Whether the storage of the state that step k (or a host evaluation at
 // the held state k) works on is not the cell order of the last sort: always
 // without reordering, else after a rebuild that kept the storage order
@@ -1586,10 +1749,188 @@ __device__ __forceinline__ bool unordered(SlotC &S, const Ctl &C, int64_t k, int
 // pub: thread TILE - 64 stores pubv there before the tile's last barrier
 // (the step kernel's next tile, published to the workgroup without a
 // barrier of its own).
-template <typename R, bool ACC, bool MIX>
-__device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k, int mode, bool cells,
-                          bool build, bool last, bool bin_next, int *pub, int pubv) {
-  const int i = lt * TILE + threadIdx.x;
+// COH: a cell step of k_run (other workgroups of this launch wrote r(k); see
+// ld).
+// unord(): whether the atoms are not in cell order (asked again where needed
+// instead of held).  si: index of the step in the replay.
+template <bool MIX>
+struct StepLds {
+  // 4 slots of padding: a group of candidates may read up to 3 slots past the
+  // window's last
+  double sx[WCAP + 4], sy[WCAP + 4], sz[WCAP + 4];
+  Window win;
+  // a mixture: the pair table and the window's species
+  typename std::conditional<MIX, PairTab, char>::type tab;
+  int8_t ssp[MIX ? WCAP + 4 : 1];
+  unsigned long long sv[4];
+  double sh[4][8];
+};
+// The end of a tile's step: (d), (e) and the next (a) -- x and v become those
+// of the next step -- the binning of r(k+1) where bin_next, the clearing of
+// the set after next (clear), and the tile's maximum speed and properties.
+// put_v: v goes to memory (k_run keeps it in registers from step to step).
+template <typename R, bool ACC, bool COH, class Lds>
+__device__ __forceinline__ void finish_tile(SlotC &S, CtlDev &C, Lds &lds, int lt, int64_t k,
+                                            int mode, bool last, bool bin_next, bool clear,
+                                            bool put_v, double (&x)[3], double (&v)[3],
+                                            const Acc<R> &a, int m, int si, int *pub, int pubv) {
+  const int tid = tid_here();
+  // (d), (e) and the next (a)
+  const int i = lt * TILE + tid;
+  const bool act = i < S.n, force = mode != MODE_BUILD;
+  const int pb = (int)(k & 1);
+  double vv = 0.0;
+  if (act && force) {
+    const double f[3] = {(double)a.fx, (double)a.fy, (double)a.fz};
+    if (mode == MODE_STEP)
+      for (int q = 0; q < 3; ++q) v[q] = v[q] + S.hdt * f[q];  // (d)
+    vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];            // (e)
+    if (mode == MODE_STEP) {
+      if (!last) {
+        double xn[3];
+        for (int q = 0; q < 3; ++q) {
+          v[q] = v[q] + S.hdt * f[q];  // (a) of step k+1
+          xn[q] = x[q] + S.dt * v[q];
+          // streaming stores: the next step's kernels read these from
+          // any XCD, so they are not kept in this XCD's L2 (less for its
+          // write-back when the kernel ends)
+          x[q] = xn[q];
+          if (COH)
+            st<true>(&gp(S.P[pb ^ 1][q])[i], xn[q]);
+          else
+            __builtin_nontemporal_store(xn[q], &gp(S.P[pb ^ 1][q])[i]);
+        }
+        if (bin_next)
+          bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
+        else
+          check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+      }
+      if (put_v)
+        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(v[q], &gp(S.V[pb ^ 1][q])[i]);
+    }
+    if (mode != MODE_STEP || last) {
+      auto F = gp((R *)S.F);
+      F[i] = a.fx;
+      F[S.npad + i] = a.fy;
+      F[2 * S.npad + i] = a.fz;
+      auto U = gp((R *)S.UA);
+      U[i] = a.u;
+      U[S.npad + i] = a.w;
+    }
+  }
+
+  // the set after next is cleared for the binning of step k+2
+  if (mode == MODE_STEP && clear) {
+    const int zs = (int)mod3(k + 2);
+    const int c0 = lt * S.cpt, c1 = min(c0 + S.cpt, S.ncell);
+    for (int c = c0 + tid; c < c1; c += TILE) st<COH>(&gp(S.cnt[zs])[c], 0);
+    for (int q = lt * TILE + tid; q < S.nctiles; q += S.ntiles * TILE)
+      st<COH>(&gp(S.tcnt[zs])[q], 0);
+    if (lt == 0 && tid == 0) st<COH>(&gp(S.ovf_n)[zs], 0);
+  }
+
+  // the maximum speed of the step (the rebuild rule needs it every step):
+  // v^2 >= 0, so its bit pattern orders like the value
+  auto &sv = lds.sv;
+  const int w = tid >> 6, l = tid & 63;
+  const unsigned long long vbits = wave_max_u64((unsigned long long)__double_as_longlong(vv));
+  if (l == 0) sv[w] = vbits;
+  // the other properties only where somebody reads them: the last step of a
+  // run, evaluations of a held state, and the steps of a block
+  const bool full = mode != MODE_STEP || last || ACC;
+  auto &sh = lds.sh;
+  if (full) {
+    const int mm = act && !S.cell_only ? m : 0;
+    const double ke = wave_sum(vv);
+    const double sm = wave_sum((double)mm);
+    const int mmax = wave_max_i(mm);
+    double pe_hi, pe_lo, vr_hi, vr_lo;
+    if (sizeof(R) == 8) {
+      pe_hi = wave_sum((double)a.u);
+      vr_hi = wave_sum((double)a.w);
+      pe_lo = vr_lo = 0.0;
+    } else {
+      F2 pe = wave_sum_f2(F2{(float)a.u, 0.0f});
+      F2 vr = wave_sum_f2(F2{(float)a.w, 0.0f});
+      pe_hi = pe.hi;
+      pe_lo = pe.lo;
+      vr_hi = vr.hi;
+      vr_lo = vr.lo;
+    }
+    if (l == 0) {
+      sh[w][0] = ke;
+      sh[w][2] = pe_hi;
+      sh[w][3] = pe_lo;
+      sh[w][4] = vr_hi;
+      sh[w][5] = vr_lo;
+      sh[w][6] = sm;
+      sh[w][7] = (double)mmax;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const unsigned long long b01 = sv[0] > sv[1] ? sv[0] : sv[1];
+    const unsigned long long b23 = sv[2] > sv[3] ? sv[2] : sv[3];
+    const unsigned long long vmb = b01 > b23 ? b01 : b23;
+    // one atomic per workgroup, spread over VSPREAD cache lines
+    if (force) atomicMax(&S.vring[(mod3(k) * VSPREAD + (lt & (VSPREAD - 1))) * 16], vmb);
+    if (full) {
+      auto q = gp(S.part) + (size_t)lt * NPART;
+      if (force) {
+        q[0] = ((sh[0][0] + sh[1][0]) + sh[2][0]) + sh[3][0];
+        q[1] = __longlong_as_double((long long)vmb);
+        if (sizeof(R) == 8) {
+          q[2] = ((sh[0][2] + sh[1][2]) + sh[2][2]) + sh[3][2];
+          q[3] = 0.0;
+          q[4] = ((sh[0][4] + sh[1][4]) + sh[2][4]) + sh[3][4];
+          q[5] = 0.0;
+        } else {
+          F2 e{(float)sh[0][2], (float)sh[0][3]}, v2{(float)sh[0][4], (float)sh[0][5]};
+          for (int k2 = 1; k2 < 4; ++k2) {
+            e = f2_add(e, F2{(float)sh[k2][2], (float)sh[k2][3]});
+            v2 = f2_add(v2, F2{(float)sh[k2][4], (float)sh[k2][5]});
+          }
+          q[2] = e.hi;
+          q[3] = e.lo;
+          q[4] = v2.hi;
+          q[5] = v2.lo;
+        }
+      }
+      q[6] = ((sh[0][6] + sh[1][6]) + sh[2][6]) + sh[3][6];
+      q[7] = fmax(fmax(sh[0][7], sh[1][7]), fmax(sh[2][7], sh[3][7]));
+      if (ACC && mode == MODE_STEP) {
+        // this tile's part of the block sums (the tile's atoms change at a
+        // sort, the total over tiles does not)
+        auto A = gp(S.acc) + (size_t)lt * NACC;
+        A[0] = A[0] + q[0];
+        A[1] = A[1] + (q[2] + q[3]);
+        A[2] = A[2] + (q[4] + q[5]);
+        A[3] = A[3] + q[6];
+        if (S.tpart) {
+          // a traced replica: this step's tile partials, reduced by k_trace
+          // at the end of the replay
+          auto Q = gp(S.tpart) + ((size_t)si * S.ntiles + lt) * 4;
+          Q[0] = q[0];
+          Q[1] = q[2] + q[3];
+          Q[2] = q[4] + q[5];
+          Q[3] = q[1];
+        }
+      }
+    }
+  }
+  if (pub != nullptr && tid == TILE - 64) *pub = pubv;
+  __syncthreads();
+}
+
+template <typename R, bool ACC, bool MIX, bool COH, class Unord>
+__device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, StepLds<MIX> &lds, int lt, int64_t k,
+                                          int mode, bool cells, bool build, bool last,
+                                          bool bin_next, bool clear, Unord unord, int si, int *pub,
+                                          int pubv) {
+  const int tid = tid_here();
+  double *const sx = lds.sx, *const sy = lds.sy, *const sz = lds.sz;
+  Window &win = lds.win;
+  const int i = lt * TILE + tid;
   const bool act = i < S.n;
   const int pb = (int)(k & 1);
   const int vb = mode == MODE_STEP ? pb : pb ^ 1;  // v(k-1/2) during a run, v(k) when clean
@@ -1607,7 +1948,8 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
   // first NE, the bulk of a long list such as LJ r_c = 3's, are read plainly:
   // such lists stay in the last-level cache from step to step.)
   constexpr int NE = sizeof(R) == 8 ? 8 : 12;
-  const bool list = !cells && force;
+  if constexpr (COH) cells = true;  // (k_run's list steps are own_step's)
+  const bool list = !COH && !cells && force;
   const auto Wc = gp((const int32_t *)S.W) + i;
   const size_t np = (size_t)S.npad;
   double xi = 0, yi = 0, zi = 0, v[3] = {0.0, 0.0, 0.0};
@@ -1615,11 +1957,11 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
   uint32_t e[NE];
   // the window table first: the staging waits for it, not for the rest
   int wtv = 0;
-  if (list && threadIdx.x < WSTRIDE) wtv = gp((const int32_t *)S.win)[lt * WSTRIDE + threadIdx.x];
+  if (list && tid < WSTRIDE) wtv = gp((const int32_t *)S.win)[lt * WSTRIDE + tid];
   if (act) {
-    xi = X[i];
-    yi = Y[i];
-    zi = Z[i];
+    xi = ld<COH>(&X[i]);
+    yi = ld<COH>(&Y[i]);
+    zi = ld<COH>(&Z[i]);
     if (force)
       for (int q = 0; q < 3; ++q) v[q] = __builtin_nontemporal_load(&gp(S.V[vb][q])[i]);
     if (list) {
@@ -1632,25 +1974,16 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
     }
   }
 
-  // the tile's LDS window: made with the list at a sort, read back otherwise
-  // (4 slots of padding: a traversal group may read up to 3 slots past the
-  // window's last)
-  __shared__ double sx[WCAP + 4], sy[WCAP + 4], sz[WCAP + 4];
-  __shared__ Window win;
-  // a mixture: the window's species and the pair table (the barriers below
-  // publish them)
-  __shared__ typename std::conditional<MIX, PairTab, char>::type stab;
-  __shared__ int8_t ssp_store[MIX ? WCAP + 4 : 1];
   const PairTab *tab = nullptr;
   int8_t *ssp = nullptr;
   const gcint SP = gp((const int32_t *)S.sp);
   int spi = 0;
   if constexpr (MIX) {
-    tab = &stab;
-    ssp = ssp_store;
+    tab = &lds.tab;
+    ssp = lds.ssp;
     constexpr int NT = (int)(sizeof(PairTab) / sizeof(double));
-    if (threadIdx.x < NT)
-      ((double *)&stab)[threadIdx.x] = gp((const double *)S.tab)[threadIdx.x];
+    if (tid < NT)
+      ((double *)&lds.tab)[tid] = gp((const double *)S.tab)[tid];
     if (act) spi = SP[i];
   }
   // a cell step: the bounds of the first neighbour row of the traversal go
@@ -1658,13 +1991,13 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
   int b0[4] = {0, 0, 0, 0};
   if (cells && act) {
     const int G = S.G;
-    row_bounds(cview((const int32_t *)S.cs), G, ci % G, (ci / G) % G, ci / (G * G), 0, b0);
+    row_bounds(gp((const int32_t *)S.cs), G, ci % G, (ci / G) % G, ci / (G * G), 0, b0);
   }
-  if (cells && unordered(S, *cview(&C), k, mode)) {
+  if (cells && unord()) {
     // no reordering: the tile's atoms are not a run of cells, so there is no
     // window; candidates are read from global memory through perm, and the
     // list steps until the next sort stage nothing
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       win.wt[0] = -1;
       win.whole = 0;
       win.rf = 0;
@@ -1674,13 +2007,13 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
   } else if (cells) {
     make_window(S, lt, win, (int *)sx);
   } else if (list) {
-    if (threadIdx.x < WSTRIDE) win.wt[threadIdx.x] = wtv;
+    if (tid < WSTRIDE) win.wt[tid] = wtv;
     __syncthreads();
   }
   // a cell step over atoms in cell order: which candidates are near comes from
   // their packed positions, while the window's loads are in flight
-  const bool near = cells && S.pk_lim != 0 && !unordered(S, *cview(&C), k, mode);
-  if (cells) stage_window<MIX>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
+  const bool near = cells && S.pk_lim != 0 && !unord();
+  if (cells) stage_window<MIX, COH>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
   int mr = 0;
   if (near && build && act) {
     // the list with its few entries that are only nearly near; an atom with
@@ -1710,14 +2043,14 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
       gs[u] = 0;
       if (u < m && (e[u] & GFLAG) && m <= S.mcap && act) {
         const uint32_t idx = e[u] & IDX_MASK;
-        gx[u] = X[idx];
-        gy[u] = Y[idx];
-        gz[u] = Z[idx];
+        gx[u] = ld<COH>(&X[idx]);
+        gy[u] = ld<COH>(&Y[idx]);
+        gz[u] = ld<COH>(&Z[idx]);
         if (MIX) gs[u] = SP[idx];
       }
     }
   }
-  if (list) stage_window<MIX>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
+  if (list) stage_window<MIX, COH>(win.wt, X, Y, Z, sx, sy, sz, SP, ssp);
   if (cells || list) __syncthreads();
 
   Acc<R> a{(R)0, (R)0, (R)0, (R)0, (R)0};
@@ -1768,7 +2101,7 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
           } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-              entry_pos<MIX>(eg[u], X, Y, Z, sx, sy, sz, xj[u], yj[u], zj[u], SP, ssp, sj[u]);
+              entry_pos<MIX, COH>(eg[u], X, Y, Z, sx, sy, sz, xj[u], yj[u], zj[u], SP, ssp, sj[u]);
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u)
@@ -1782,74 +2115,28 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
         near_atoms(S, i, ci, win, pk_array(S, k), b0, [&](uint32_t e1) {
           double xj, yj, zj;
           int sj = 0;
-          entry_pos<MIX>(e1, X, Y, Z, sx, sy, sz, xj, yj, zj, SP, ssp, sj);
+          entry_pos<MIX, COH>(e1, X, Y, Z, sx, sy, sz, xj, yj, zj, SP, ssp, sj);
           (void)pair(e1, xj, yj, zj, sj);
         });
       }
     } else if (cells) {
-      m = traverse_sorted<R, MIX>(S, i, ci, X, Y, Z, win, sx, sy, sz, xi, yi, zi, build, force,
+      m = traverse_sorted<R, MIX, COH>(S, i, ci, X, Y, Z, win, sx, sy, sz, xi, yi, zi, build, force,
                                   mode != MODE_STEP || last || ACC, a, ssp, SP, spi, tab,
-                                  unordered(S, *cview(&C), k, mode), false, b0);
+                                  unord(), false, b0);
       if (build) gp(S.m)[i] = m;
     } else if (list) {
       if (m <= S.mcap) {
         const double rc2 = S.rc2;
         const R ushift = (R)S.ushift;
         const bool energy = mode != MODE_STEP || last || ACC;
-        // entries in order, four at a time (their coordinate reads together),
-        // for as long as any lane of the wave has some left: a lane past its
-        // length takes the group with no effect, so the wave runs max(m)/4
-        // groups whatever the spread of m.  A group without image codes
-        // anywhere in the wave skips the shifts.
-        // PRE: entries q0 .. q0+3 are among the first NP (their global
-        // coordinates gathered above)
+        // entries in order, four at a time, for as long as any lane of the wave
+        // has some left: a lane past its length takes the group with no effect,
+        // so the wave runs max(m)/4 groups whatever the spread of m
         auto group = [&](auto pre, int q0, uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) {
-          constexpr bool PRE = decltype(pre)::value;
-          const bool ok[4] = {q0 < m, q0 + 1 < m, q0 + 2 < m, q0 + 3 < m};
-          const uint32_t eg[4] = {ok[0] ? e0 : 0u, ok[1] ? e1 : 0u, ok[2] ? e2 : 0u,
-                                  ok[3] ? e3 : 0u};
-          const uint32_t any = (eg[0] | eg[1]) | (eg[2] | eg[3]);
-          double xj[4], yj[4], zj[4];
-          int sj[4] = {0, 0, 0, 0};
-          if (__ballot((any & GFLAG) != 0) == 0) {
-            // the usual case: every entry of the wave is a window slot
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const uint32_t sl = eg[u] & IDX_MASK;
-              xj[u] = sx[sl];
-              yj[u] = sy[sl];
-              zj[u] = sz[sl];
-              if (MIX) sj[u] = ssp[sl];
-            }
-          } else if constexpr (PRE) {
-            // window slots from LDS (slot 0 for an entry outside it), the
-            // others from the gathered coordinates
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool g = (eg[u] & GFLAG) != 0;
-              const uint32_t sl = g ? 0u : eg[u] & IDX_MASK;
-              const int qu = min(q0 + u, NP - 1);
-              xj[u] = g ? gx[qu] : sx[sl];
-              yj[u] = g ? gy[qu] : sy[sl];
-              zj[u] = g ? gz[qu] : sz[sl];
-              if (MIX) sj[u] = g ? gs[qu] : ssp[sl];
-            }
-          } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              entry_pos<MIX>(eg[u], X, Y, Z, sx, sy, sz, xj[u], yj[u], zj[u], SP, ssp, sj[u]);
-          }
-          if (__ballot((any >> J_BITS) != 0) == 0) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              list_pair<R, false, MIX>(a, ok[u], eg[u], xi, yi, zi, xj[u], yj[u], zj[u], L, rc2,
-                                       ushift, energy, (spi * MAXSP + sj[u]) & (MAXSP * MAXSP - 1), tab);
-          } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              list_pair<R, true, MIX>(a, ok[u], eg[u], xi, yi, zi, xj[u], yj[u], zj[u], L, rc2,
-                                      ushift, energy, (spi * MAXSP + sj[u]) & (MAXSP * MAXSP - 1), tab);
-          }
+          list_group<R, MIX, COH, decltype(pre)::value, NP>(a, q0, m, {e0, e1, e2, e3}, X, Y, Z, sx,
+                                                            sy, sz, xi, yi, zi, L, rc2, ushift,
+                                                            energy, tab, spi, SP, ssp, gx, gy, gz,
+                                                            gs);
         };
 #pragma unroll
         for (int g = 0; g < NP / 4; ++g)
@@ -1870,152 +2157,122 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, int lt, int64_t k
         // atom over the 27 cells of its cell at that sort, with the positions
         // of now (exact: an atom within r_c now was within r_n then, since
         // neither moved more than delta/2), reading them from global memory
-        traverse_sorted<R, MIX>(S, i, gp(S.cell)[i], X, Y, Z, win, sx, sy, sz, xi, yi, zi,
+        traverse_sorted<R, MIX, COH>(S, i, gp(S.cell)[i], X, Y, Z, win, sx, sy, sz, xi, yi, zi,
                                 false, true, mode != MODE_STEP || last || ACC, a, ssp, SP, spi,
-                                tab, unordered(S, *cview(&C), k, mode), true);
+                                tab, unord(), true);
       }
     }
   }
 
-  // (d), (e) and the next (a)
-  double vv = 0.0;
-  if (act && force) {
-    const double f[3] = {(double)a.fx, (double)a.fy, (double)a.fz};
-    if (mode == MODE_STEP)
-      for (int q = 0; q < 3; ++q) v[q] = v[q] + S.hdt * f[q];  // (d)
-    vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];            // (e)
-    if (mode == MODE_STEP) {
-      if (!last) {
-        double xn[3];
-        const double xo[3] = {xi, yi, zi};
-        for (int q = 0; q < 3; ++q) {
-          v[q] = v[q] + S.hdt * f[q];  // (a) of step k+1
-          xn[q] = xo[q] + S.dt * v[q];
-          // streaming stores: the next step's kernels read these from
-          // any XCD, so they are not kept in this XCD's L2 (less for its
-          // write-back when the kernel ends)
-          __builtin_nontemporal_store(xn[q], &gp(S.P[pb ^ 1][q])[i]);
-        }
-        if (bin_next)
-          bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
-        else
-          check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+  double x[3] = {xi, yi, zi};
+  finish_tile<R, ACC, COH>(S, C, lds, lt, k, mode, last, bin_next, clear, true, x, v, a, m, si, pub,
+                           pubv);
+}
+
+// A tile that stays with its workgroup from step to step (k_run with one tile
+// per workgroup): an atom's position, velocity, list length and first NR list
+// entries are held in registers, the window's intervals (and a mixture's
+// species and pair table) in LDS, so a list step only reads its window.
+template <typename R>
+struct Own {
+  static constexpr int NR = sizeof(R) == 8 ? 12 : 20;
+  double x[3], v[3];
+  int m, sp;
+  uint32_t e[NR];
+};
+// State k of tile lt after a build (or at the start of a launch).
+template <typename R, bool MIX>
+__device__ __forceinline__ void own_load(SlotC &S, StepLds<MIX> &lds, int lt, int64_t k,
+                                         Own<R> &o) {
+  const int tid = tid_here(), i = lt * TILE + tid, pb = (int)(k & 1);
+  const auto W = gp((const int32_t *)S.W) + i;
+  const size_t np = (size_t)S.npad;
+  if (tid < WSTRIDE) lds.win.wt[tid] = gp((const int32_t *)S.win)[lt * WSTRIDE + tid];
+  if constexpr (MIX) {
+    constexpr int NT = (int)(sizeof(PairTab) / sizeof(double));
+    if (tid < NT) ((double *)&lds.tab)[tid] = gp((const double *)S.tab)[tid];
+  }
+  o.m = o.sp = 0;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) o.x[q] = o.v[q] = 0.0;
+#pragma unroll
+  for (int u = 0; u < Own<R>::NR; ++u) o.e[u] = 0u;
+  if (i < S.n) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      o.x[q] = ld<true>(&gp((const double *)S.P[pb][q])[i]);
+      o.v[q] = gp((const double *)S.V[pb][q])[i];
+    }
+    o.m = gp((const int32_t *)S.m)[i];
+    if (MIX) o.sp = gp((const int32_t *)S.sp)[i];
+#pragma unroll
+    for (int u = 0; u < Own<R>::NR; ++u) o.e[u] = u < S.mcap ? (uint32_t)W[(size_t)u * np] : 0u;
+  }
+  __syncthreads();
+  if constexpr (MIX) stage_species(lds.win.wt, gp((const int32_t *)S.sp), lds.ssp);
+}
+// A list step of the held tile (the list path of step_tile, entry for entry).
+template <typename R, bool ACC, bool MIX>
+__device__ __forceinline__ void own_step(SlotC &S, CtlDev &C, StepLds<MIX> &lds, int lt, int64_t k,
+                                         bool last, bool clear, bool unord, int si, Own<R> &o) {
+  constexpr int NR = Own<R>::NR;
+  const int tid = tid_here(), i = lt * TILE + tid, pb = (int)(k & 1);
+  const gcdouble X = gp((const double *)S.P[pb][0]);
+  const gcdouble Y = gp((const double *)S.P[pb][1]);
+  const gcdouble Z = gp((const double *)S.P[pb][2]);
+  const double *const sx = lds.sx, *const sy = lds.sy, *const sz = lds.sz;
+  const gcint SP = gp((const int32_t *)S.sp);
+  const int8_t *ssp = MIX ? lds.ssp : nullptr;
+  const PairTab *tab = nullptr;
+  if constexpr (MIX) tab = &lds.tab;
+  // (the list stays the same from step to step: what is decoded from it would
+  // be hoisted out of the step loop, 12 registers an entry, and spilled)
+  asm volatile("" : "+v"(o.m), "+v"(o.sp));
+#pragma unroll
+  for (int u = 0; u < NR; ++u) asm volatile("" : "+v"(o.e[u]));
+  stage_window<false, true>(lds.win.wt, X, Y, Z, lds.sx, lds.sy, lds.sz, SP, nullptr);
+  __syncthreads();
+  Acc<R> a{(R)0, (R)0, (R)0, (R)0, (R)0};
+  const bool energy = last || ACC;
+  if (i < S.n) {
+    const double L = S.L, rc2 = S.rc2;
+    const R ushift = (R)S.ushift;
+    const int m = o.m;
+    if (m <= S.mcap) {
+      const auto W = gp((const int32_t *)S.W) + i;
+      const size_t np = (size_t)S.npad;
+      auto group = [&](int q0, Four f) {
+        list_group<R, MIX, true, false, 4>(a, q0, m, f, X, Y, Z, sx, sy, sz, o.x[0], o.x[1], o.x[2],
+                                           L, rc2, ushift, energy, tab, o.sp, SP, ssp, nullptr,
+                                           nullptr, nullptr, nullptr);
+      };
+#pragma unroll
+      for (int g = 0; g < NR / 4; ++g)
+        if (__ballot(4 * g < m) != 0)
+          group(4 * g, {o.e[4 * g], o.e[4 * g + 1], o.e[4 * g + 2], o.e[4 * g + 3]});
+      for (int q = NR; __ballot(q < m) != 0; q += 4) {
+        Four f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) f.e[u] = q + u < m ? (uint32_t)W[(size_t)(q + u) * np] : 0u;
+        group(q, f);
       }
-      for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(v[q], &gp(S.V[pb ^ 1][q])[i]);
-    }
-    if (mode != MODE_STEP || last) {
-      auto F = gp((R *)S.F);
-      F[i] = a.fx;
-      F[S.npad + i] = a.fy;
-      F[2 * S.npad + i] = a.fz;
-      auto U = gp((R *)S.UA);
-      U[i] = a.u;
-      U[S.npad + i] = a.w;
-    }
-  }
-
-  // the set after next is cleared for the binning of step k+2
-  if (mode == MODE_STEP) {
-    const int zs = (int)mod3(k + 2);
-    const int c0 = lt * S.cpt, c1 = min(c0 + S.cpt, S.ncell);
-    for (int c = c0 + threadIdx.x; c < c1; c += TILE) gp(S.cnt[zs])[c] = 0;
-    for (int q = lt * TILE + threadIdx.x; q < S.nctiles; q += S.ntiles * TILE)
-      gp(S.tcnt[zs])[q] = 0;
-    if (lt == 0 && threadIdx.x == 0) S.ovf_n[zs] = 0;
-  }
-
-  // the maximum speed of the step (the rebuild rule needs it every step):
-  // v^2 >= 0, so its bit pattern orders like the value
-  __shared__ unsigned long long sv[4];
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const unsigned long long vbits = wave_max_u64((unsigned long long)__double_as_longlong(vv));
-  if (l == 0) sv[w] = vbits;
-  // the other properties only where somebody reads them: the last step of a
-  // run, evaluations of a held state, and the steps of a block
-  const bool full = mode != MODE_STEP || last || ACC;
-  __shared__ double sh[4][8];
-  if (full) {
-    const int mm = act && !S.cell_only ? m : 0;
-    const double ke = wave_sum(vv);
-    const double sm = wave_sum((double)mm);
-    const int mmax = wave_max_i(mm);
-    double pe_hi, pe_lo, vr_hi, vr_lo;
-    if (sizeof(R) == 8) {
-      pe_hi = wave_sum((double)a.u);
-      vr_hi = wave_sum((double)a.w);
-      pe_lo = vr_lo = 0.0;
     } else {
-      F2 pe = wave_sum_f2(F2{(float)a.u, 0.0f});
-      F2 vr = wave_sum_f2(F2{(float)a.w, 0.0f});
-      pe_hi = pe.hi;
-      pe_lo = pe.lo;
-      vr_hi = vr.hi;
-      vr_lo = vr.lo;
-    }
-    if (l == 0) {
-      sh[w][0] = ke;
-      sh[w][2] = pe_hi;
-      sh[w][3] = pe_lo;
-      sh[w][4] = vr_hi;
-      sh[w][5] = vr_lo;
-      sh[w][6] = sm;
-      sh[w][7] = (double)mmax;
+      // its list overflowed: over the 27 cells of its cell at the last sort
+      traverse_sorted<R, MIX, true>(S, i, gp(S.cell)[i], X, Y, Z, lds.win, sx, sy, sz, o.x[0],
+                                    o.x[1], o.x[2], false, true, energy, a, ssp, SP, o.sp, tab,
+                                    unord, true);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned long long b01 = sv[0] > sv[1] ? sv[0] : sv[1];
-    const unsigned long long b23 = sv[2] > sv[3] ? sv[2] : sv[3];
-    const unsigned long long vmb = b01 > b23 ? b01 : b23;
-    // one atomic per workgroup, spread over VSPREAD cache lines
-    if (force) atomicMax(&S.vring[(mod3(k) * VSPREAD + (lt & (VSPREAD - 1))) * 16], vmb);
-    if (full) {
-      auto q = gp(S.part) + (size_t)lt * NPART;
-      if (force) {
-        q[0] = ((sh[0][0] + sh[1][0]) + sh[2][0]) + sh[3][0];
-        q[1] = __longlong_as_double((long long)vmb);
-        if (sizeof(R) == 8) {
-          q[2] = ((sh[0][2] + sh[1][2]) + sh[2][2]) + sh[3][2];
-          q[3] = 0.0;
-          q[4] = ((sh[0][4] + sh[1][4]) + sh[2][4]) + sh[3][4];
-          q[5] = 0.0;
-        } else {
-          F2 e{(float)sh[0][2], (float)sh[0][3]}, v2{(float)sh[0][4], (float)sh[0][5]};
-          for (int k2 = 1; k2 < 4; ++k2) {
-            e = f2_add(e, F2{(float)sh[k2][2], (float)sh[k2][3]});
-            v2 = f2_add(v2, F2{(float)sh[k2][4], (float)sh[k2][5]});
-          }
-          q[2] = e.hi;
-          q[3] = e.lo;
-          q[4] = v2.hi;
-          q[5] = v2.lo;
-        }
-      }
-      q[6] = ((sh[0][6] + sh[1][6]) + sh[2][6]) + sh[3][6];
-      q[7] = fmax(fmax(sh[0][7], sh[1][7]), fmax(sh[2][7], sh[3][7]));
-      if (ACC && mode == MODE_STEP) {
-        // this tile's part of the block sums (the tile's atoms change at a
-        // sort, the total over tiles does not)
-        auto A = gp(S.acc) + (size_t)lt * NACC;
-        A[0] = A[0] + q[0];
-        A[1] = A[1] + (q[2] + q[3]);
-        A[2] = A[2] + (q[4] + q[5]);
-        A[3] = A[3] + q[6];
-        if (S.tpart) {
-          // a traced replica: this step's tile partials, reduced by k_trace
-          // at the end of the replay
-          const int si = (int)(k - C.base - 1);
-          auto Q = gp(S.tpart) + ((size_t)si * S.ntiles + lt) * 4;
-          Q[0] = q[0];
-          Q[1] = q[2] + q[3];
-          Q[2] = q[4] + q[5];
-          Q[3] = q[1];
-        }
-      }
-    }
-  }
-  if (pub != nullptr && threadIdx.x == TILE - 64) *pub = pubv;
-  __syncthreads();
+  finish_tile<R, ACC, true>(S, C, lds, lt, k, MODE_STEP, last, false, clear, false, o.x, o.v, a,
+                            o.m, si, nullptr, 0);
+}
+// v(k-1/2) of the held tile to memory, where state k keeps it.
+template <typename R>
+__device__ __forceinline__ void own_store(SlotC &S, int lt, int64_t k, const Own<R> &o) {
+  const int i = lt * TILE + tid_here();
+  if (i < S.n)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) gp(S.V[k & 1][q])[i] = o.v[q];
 }
 
 // ACC: every step of this launch also adds its properties to the block sums
@@ -2119,6 +2376,7 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_step(Tables T, int s, int
   const bool dyn = (gridDim.x & 7) == 0 && nt > (int)gridDim.x;
   const bool slabs = order == ORDER_SLABS;
   __shared__ int s_claim[2];
+  __shared__ StepLds<MIX> lds;
   // the tile after this one: the static walk's, or the claimed one (double-
   // buffered: a slot is written again only after the last barrier of the
   // next tile, which every thread passes after reading it)
@@ -2152,8 +2410,10 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_step(Tables T, int s, int
       C.var_ring[mod3(k)] = var;
       C.ord_ring[mod3(k)] = unordered(S, *cview(&C), k, mode) ? 1 : 0;
     }
-    step_tile<R, ACC, MIX>(S, C, lt, k, mode, cells, build, last, bin_next,
-                           dyn ? &s_claim[it & 1] : nullptr, claim);
+    step_tile<R, ACC, MIX, false>(
+        S, C, lds, lt, k, mode, cells, build, last, bin_next, true,
+        [&] { return unordered(S, *cview(&C), k, mode); }, s, dyn ? &s_claim[it & 1] : nullptr,
+        claim);
     stepped = true;
     if (mode == MODE_STEP && lt == 0 && threadIdx.x < VSPREAD)
       S.vring[(mod3(k + 1) * VSPREAD + threadIdx.x) * 16] = 0ull;
@@ -2162,6 +2422,374 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_step(Tables T, int s, int
     atomicExch(cnt, 0);
     atomicExch(fin, 0);
   }
+}
+
+// The step counters after K steps of a run from `base`.
+__device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t target, int err,
+                                        int64_t err_step) {
+  int64_t done = base + K < target ? base + K : target;
+  if (err != 0) done = err_step - 1 < done ? err_step - 1 : done;
+  if (done < C.done) done = C.done;
+  C.done = done;
+  C.base = done;
+  // a replica that ran holds a drifted state unless it finished
+  C.clean = (done == target && err == 0) ? 1 : 0;
+}
+
+// ---------------------------------------------------------------------------
+// several steps of a single system in one launch
+// ---------------------------------------------------------------------------
+// A system whose tiles all fit on the chip at once (1 024 of them, 262 144
+// atoms) spends most of a step between kernels: at N = 110 592 a step of two
+// launches took 25 us, 10 of them tile work.  k_run keeps its workgroups, one
+// per tile, through `steps` steps and separates the steps by a barrier over
+// the grid (1.5-2.4 us at 8-1 000 workgroups, against ~4 us for a kernel
+// boundary and ~4.5 us for a sort launch that finds nothing to sort); the
+// sort runs between two barriers of a rebuild step.
+//
+// Who takes part: a barrier over workgroups needs all of them running, and
+// what else the GPU does is not known here (another stream, another process).
+// So each launch begins with a roll call: a workgroup counts itself in, and
+// the launch is committed to the workgroups present, to all of them once the
+// last has come, or to those that have come when one has waited ROLL_TICKS.
+// The others find the launch committed without them and leave.  Everybody
+// who takes part is running and stays so, so every barrier completes, and
+// with fewer participants than tiles each steps several.  (The spin bound of
+// the barriers is a backstop: it latches ERR_STALL.)
+//
+// What is shared: positions and the cell counters cross between workgroups
+// with device-scope loads and stores (ld, st), so an ordinary step needs no
+// cache maintenance; the barriers around a sort, whose plain stores are read
+// by other workgroups, are full release/acquire fences.  A tile's velocities,
+// list and window are only touched by its own workgroup between sorts.
+constexpr long long ROLL_TICKS = 10000;  // 100 us of the 100 MHz clock
+constexpr int RUN_SPINS = 1 << 22;
+// Words of Tables::run, each on its own 256-byte line; zero between launches.
+enum { RUN_GROUPS = 32, RUN_ROOT = 32, RUN_EPOCH = 33, RUN_ARRIVE = 34, RUN_STATE = 35,
+       RUN_EXIT = 36, RUN_XROOT = 37, RUN_XEPOCH = 38, RUN_XCNT = 40, RUN_XARR = 56, RUN_XFLAG = 72,
+       RUN_LINES = 88 };
+constexpr int MAX_XCD = 16;
+static_assert(RUN_LINES * 256 <= RUN_BYTES, "Tables::run");
+
+// What a participant knows of the others: its place among n, its XCD, how
+// many participants share it (0: not everybody is present, so nobody has
+// counted them) and how many XCDs there are.
+struct RunSeat {
+  int32_t *w;
+  int rank, n, xcd, inx, nx;
+  int epoch, xepoch;  // barriers and fences passed
+};
+// The maximum speed of a ring entry and the error word as of a barrier.
+struct RunOut {
+  unsigned long long vbits;
+  int err;
+};
+__device__ __forceinline__ bool run_wait(int32_t *f, int v) {
+  for (int it = 0; it < RUN_SPINS; ++it) {
+    if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= v) return true;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return false;
+}
+
+// The grid barrier.  Arrivals are counted in 32 groups, then over the groups:
+// 1 000 workgroups on one counter took 12.7 us, in 32 groups 2.0.
+// full: everything stored before it is seen after it.  A write-back or an
+// invalidation acts on a whole XCD's L2, so one workgroup per XCD, the last
+// there to arrive, writes it back, and invalidates it when all XCDs have; the
+// others then only drop their CU's L1.  (By every wave the two fences took
+// 70 us and 45 us at 1 000 workgroups.)
+// The maximum speed of ring entry e (e < 0: none) and the error word are left
+// in `out`.
+__device__ __forceinline__ void run_barrier(RunSeat &p, bool full, SlotC &S0, CtlDev &C, int e,
+                                            RunOut &out) {
+  constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
+  int32_t *w = p.w;
+  const bool all = p.inx > 0;
+  if (full && !all) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have arrived
+  __syncthreads();
+  if (full && all)
+    ++p.xepoch;
+  else
+    ++p.epoch;
+  if (threadIdx.x < 64) {
+    bool ok = true;
+    if (threadIdx.x == 0) {
+      if (full && all) {
+        if (__hip_atomic_fetch_add(&w[64 * (RUN_XARR + p.xcd)], 1, __ATOMIC_RELAXED, AG) ==
+            p.xepoch * p.inx - 1) {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+          if (__hip_atomic_fetch_add(&w[64 * RUN_XROOT], 1, __ATOMIC_RELAXED, AG) ==
+              p.xepoch * p.nx - 1)
+            __hip_atomic_store(&w[64 * RUN_XEPOCH], p.xepoch, __ATOMIC_RELAXED, AG);
+          ok = run_wait(&w[64 * RUN_XEPOCH], p.xepoch);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          __hip_atomic_store(&w[64 * (RUN_XFLAG + p.xcd)], p.xepoch, __ATOMIC_RELAXED, AG);
+        } else {
+          ok = run_wait(&w[64 * (RUN_XFLAG + p.xcd)], p.xepoch);
+        }
+      } else {
+        const int g = p.rank & (RUN_GROUPS - 1), in = (p.n - g + RUN_GROUPS - 1) / RUN_GROUPS;
+        const int ng = p.n < RUN_GROUPS ? p.n : RUN_GROUPS;
+        if (__hip_atomic_fetch_add(&w[64 * g], 1, __ATOMIC_RELAXED, AG) == p.epoch * in - 1 &&
+            __hip_atomic_fetch_add(&w[64 * RUN_ROOT], 1, __ATOMIC_RELAXED, AG) ==
+                p.epoch * ng - 1)
+          __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch, __ATOMIC_RELAXED, AG);
+        ok = run_wait(&w[64 * RUN_EPOCH], p.epoch);
+      }
+    }
+    if (!ok) atomicOr(&C.err, ERR_STALL);
+    __builtin_amdgcn_s_waitcnt(0);
+    if (full && all) asm volatile("buffer_inv sc0" ::: "memory");  // this CU's L1
+    unsigned long long v = 0;
+    if (e >= 0 && threadIdx.x < VSPREAD)
+      v = __hip_atomic_load(&S0.vring[(e * VSPREAD + threadIdx.x) * 16], __ATOMIC_RELAXED, AG);
+    const int err = __hip_atomic_load(&C.err, __ATOMIC_RELAXED, AG);
+    v = wave_max_u64(v);
+    if (threadIdx.x == 0) {
+      out.vbits = v;
+      out.err = err;
+    }
+  }
+  __syncthreads();
+  if (full && !all) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// Steps done + 1 .. min(done + steps, target) of the one replica of T.
+// commit: also the step counters (a traced replica's are advanced after its
+// trace has been reduced).
+template <typename R, bool ACC, bool MIX>
+__global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, long long target,
+                                                         int commit) {
+  constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
+  __shared__ StepLds<MIX> lds;
+  // (every thread has read `out` and the roll call before a tile's first
+  // barrier, after which the tile writes these words)
+  RunOut &out = *(RunOut *)lds.sh;
+  int &s_rank = ((int *)lds.sv)[0], &s_n = ((int *)lds.sv)[1];
+  static_assert(sizeof(SortLds) <= sizeof(lds.sx), "the sort's LDS shares the window's");
+  SortLds &slds = *(SortLds *)lds.sx;
+  int32_t *w = T.run;
+  CtlDev &C = T.ctl[0];
+  SlotC &S0 = slot(T, 0);
+  // the control words as earlier launches left them (this launch writes them
+  // only after the roll call)
+  const auto &C0 = *cview(T.ctl);
+  const int64_t done = C0.done, force_step = C0.force_step, bins_step = C0.bins_step;
+  const int64_t end = done + steps < target ? done + steps : target;
+  const bool clean = C0.clean != 0, cell_only = S0.cell_only != 0;
+  int64_t k = done + 1;
+  double D2 = C0.disp_ring[mod3(k - 2)];
+  double V1 = uniform(ring_max(S0, mod3(k - 1))), V2 = uniform(ring_max(S0, mod3(k - 2)));
+  int var = C0.var_ring[mod3(k - 1)];
+  int64_t reo1 = C0.reo_ring[mod3(k - 1)];
+  bool ord = C0.ord_ring[mod3(k - 1)] != 0;
+  const bool idle = C0.err != 0 || done >= end;
+  // (read here: a workgroup that comes after the others have gone on may find
+  // other words, and takes no part)
+  asm volatile("" ::"s"(done), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean));
+  // roll call
+  // (XCC_ID, hardware register 20, 4 bits)
+  RunSeat me;
+  me.w = w;
+  me.epoch = me.xepoch = 0;
+  me.xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (MAX_XCD - 1);
+  if (threadIdx.x == 0) {
+    (void)__hip_atomic_fetch_add(&w[64 * (RUN_XCNT + me.xcd)], 1, __ATOMIC_RELAXED, AG);
+    __builtin_amdgcn_s_waitcnt(0);  // (counted there before it is counted present)
+    const int rank = __hip_atomic_fetch_add(&w[64 * RUN_ARRIVE], 1, __ATOMIC_RELAXED, AG);
+    int n = 0, zero = 0;
+    if (rank == (int)gridDim.x - 1)
+      __hip_atomic_compare_exchange_strong(&w[64 * RUN_STATE], &zero, rank + 1, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, AG);
+    const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
+    while ((n = __hip_atomic_load(&w[64 * RUN_STATE], __ATOMIC_RELAXED, AG)) == 0) {
+      if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > ROLL_TICKS) {
+        zero = 0;
+        __hip_atomic_compare_exchange_strong(
+            &w[64 * RUN_STATE], &zero,
+            __hip_atomic_load(&w[64 * RUN_ARRIVE], __ATOMIC_RELAXED, AG), __ATOMIC_RELAXED,
+            __ATOMIC_RELAXED, AG);
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    s_rank = rank;
+    s_n = n;
+  }
+  __syncthreads();
+  const int n = __builtin_amdgcn_readfirstlane(s_n);
+  const bool all = n == (int)gridDim.x;
+  // with everybody present a workgroup's place goes by its number, so that
+  // each XCD has a contiguous eighth of the tiles; else by its arrival
+  const int rank = all ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(s_rank);
+  if (rank < n) {
+    me.rank = rank;
+    me.n = n;
+    me.inx = me.nx = 0;
+    if (all) {
+      const int l = threadIdx.x & 63;
+      const int c = l < MAX_XCD ? __hip_atomic_load(&w[64 * (RUN_XCNT + l)], __ATOMIC_RELAXED, AG)
+                                : 0;
+      me.nx = __popcll(__ballot(c > 0));
+      me.inx = __builtin_amdgcn_readlane(c, me.xcd);
+    }
+    const int nt = S0.ntiles, per = (nt + 7) >> 3;
+    const int first = all ? (rank & 7) * per + (rank >> 3) : rank;
+    // (all present: grid = 8 per, one tile each and none for some)
+    const int tend = all ? min(nt, ((rank & 7) + 1) * per) : nt, tstep = all ? nt : n;
+    // shares of a cell tile: as many units as participants where that leaves a
+    // share an atom or so per thread
+    const int nsp = max(1, min(8, n / S0.nctiles)), nunits = S0.nctiles * nsp;
+    const bool lead = rank == 0 && threadIdx.x == 0;
+    int err = idle ? 1 : 0;  // nothing to do: the loop below is not entered
+    if (lead) {
+      C.target = target;
+      C.base = done;
+    }
+    // With a list, a sort's positions are binned when the rule has fired: here
+    // that is a barrier more, where binning ahead (see bins_rule) costs a step
+    // its atomics and a full barrier about one and a half times per rebuild.
+    // With the cell method every step bins the next one's.
+    bool binned = cell_only || k == bins_step;
+    int dirty = 7;  // cell-layer sets to be cleared (as far as is known)
+    if (clean && !idle) {
+      for (int t = first; t < tend; t += tstep) kick_tile<true>(slot(T, var), C, t, done, binned);
+      run_barrier(me, binned, S0, C, -1, out);
+      err = __builtin_amdgcn_readfirstlane(out.err);
+    }
+    // the decisions of k_sort for step k
+    double d1 = 0.0;
+    bool rebuild = true, reo = true;
+    // (the loop's state is the same in every lane, but the compiler loses that
+    // through the barriers' one-lane branches: without this it held the step
+    // number and the descriptors in vector registers and spilled them)
+    auto scalars = [&] {
+      k = uniform(k);
+      var = uniform(var);
+      reo1 = uniform(reo1);
+      ord = uniform(ord);
+      dirty = uniform(dirty);
+      D2 = uniform(D2);
+      V1 = uniform(V1);
+      V2 = uniform(V2);
+      binned = uniform(binned);
+    };
+    auto decide = [&] {
+      scalars();
+      d1 = 0.0;
+      rebuild = true;
+      if (!cell_only) rebuild = uniform(rebuild_rule(S0, force_step, k, D2, V1, &d1));
+      d1 = uniform(d1);
+      reo = !S0.noreo && (S0.nr <= 0 || k - reo1 >= S0.nr);
+    };
+    auto record = [&] {
+      if (!lead) return;
+      C.rb_ring[mod3(k)] = rebuild ? (reo ? RB_REORDER : RB_PERM) : RB_NONE;
+      C.bin_ring[mod3(k)] = 0;
+      C.reo_ring[mod3(k)] = reo1;
+      if (!cell_only) {
+        C.disp_ring[mod3(k - 1)] = d1;
+        if (rebuild && k != force_step) C.n_rebuilds += 1;
+      }
+      C.var_ring[mod3(k)] = var;
+      C.ord_ring[mod3(k)] = ord ? 1 : 0;
+    };
+    auto to_clear = [&] {
+      const int set = (int)mod3(k + 2);
+      const bool c = (dirty >> set & 1) != 0;
+      dirty &= ~(1 << set);
+      return c;
+    };
+    // the end of step k, with its barrier
+    auto next = [&](bool full) {
+      if (first == 0 && threadIdx.x < VSPREAD)
+        st<true>(&gp(S0.vring)[(mod3(k + 1) * VSPREAD + threadIdx.x) * 16], 0ull);
+      run_barrier(me, full, S0, C, (int)mod3(k), out);
+      err = __builtin_amdgcn_readfirstlane(out.err);
+      D2 = d1;
+      V2 = V1;
+      V1 = uniform(__longlong_as_double((long long)out.vbits));
+      binned = cell_only;
+      ++k;
+    };
+    while (k <= end && err == 0) {
+      decide();
+      if (!rebuild) {
+        // the list steps up to the next rebuild; with one tile per workgroup it
+        // is held from step to step
+        const bool unord = ord || S0.noreo;
+        Own<R> own;
+        bool held = false;
+        do {
+          SlotC &S = slot(T, var);
+          record();
+          const bool clear = to_clear();
+          for (int t = first; t < tend; t += tstep) {
+            if (!held) own_load<R, MIX>(S, lds, t, k, own);
+            own_step<R, ACC, MIX>(S, C, lds, t, k, k == target, clear, unord, (int)(k - done - 1),
+                                  own);
+            if (!all) own_store(S, t, k + 1, own);
+          }
+          held = all;
+          next(false);
+          if (k > end || err != 0) break;
+          decide();
+        } while (!rebuild);
+        if (all && first < tend) own_store(slot(T, var), first, k, own);
+        if (k > end || err != 0) break;
+      }
+      scalars();
+      const int set = (int)mod3(k);
+      if (!binned) {
+        SlotC &S = slot(T, var);
+        const int pb = (int)(k & 1);
+        for (int t = first; t < tend; t += tstep) {
+          const int i = t * TILE + tid_here();
+          if (i < S.n)
+            bin_atom(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
+                     ld<true>(&gp((const double *)S.P[pb][1])[i]),
+                     ld<true>(&gp((const double *)S.P[pb][2])[i]), k);
+        }
+        // (counted where binning ahead would have missed it)
+        if (lead && !uniform(bins_rule(S0, force_step, k, D2, V2))) C.late_bins += 1;
+        run_barrier(me, true, S0, C, -1, out);
+        err = __builtin_amdgcn_readfirstlane(out.err);
+        if (err != 0) break;
+      }
+      scalars();
+      SortRun sr;
+      for (int u = rank; u < nunits; u += n) {
+        const int t = u / nsp;
+        sort_unit(slot(T, var), slot(T, var ^ 1), C, k, MODE_STEP, reo, t, u - t * nsp, nsp, 0,
+                  sr, slds);
+      }
+      run_barrier(me, true, S0, C, -1, out);
+      if (reo) var ^= 1;
+      ord = !reo;
+      if (reo) reo1 = k;
+      dirty |= 1 << set;
+      scalars();
+      record();
+      const bool unord = ord || S0.noreo, clear = to_clear(), bin1 = cell_only && k != target;
+      for (int t = first; t < tend; t += tstep)
+        step_tile<R, ACC, MIX, true>(slot(T, var), C, lds, t, k, MODE_STEP, true, !cell_only,
+                                     k == target, bin1, clear,
+                                     [&] { return unord; }, (int)(k - done - 1), nullptr, 0);
+      next(bin1);
+    }
+    if (lead && commit && !idle) {
+      const int64_t es = (int64_t)__hip_atomic_load((unsigned long long *)&C.err_step,
+                                                   __ATOMIC_RELAXED, AG);
+      end_run(C, (int)(end - done), done, target,
+              __hip_atomic_load(&C.err, __ATOMIC_RELAXED, AG), es);
+    }
+  }
+  // the last to leave clears the words for the next launch
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(&w[64 * RUN_EXIT], 1, __ATOMIC_RELAXED, AG) == (int)gridDim.x - 1)
+    for (int q = 0; q < RUN_LINES; ++q)
+      __hip_atomic_store(&w[64 * q], 0, __ATOMIC_RELAXED, AG);
 }
 
 // End of a graph replay of K steps, before k_replay_end: for every traced
@@ -2212,13 +2840,7 @@ __global__ void k_replay_end(Tables T, int K) {
   CtlDev &C = T.ctl[r];
   if (slot(T, 2 * r).n <= 0) return;
   if (C.base >= C.target && C.done >= C.target) return;
-  int64_t done = C.base + K < C.target ? C.base + K : C.target;
-  if (C.err != 0) done = C.err_step - 1 < done ? C.err_step - 1 : done;
-  if (done < C.done) done = C.done;
-  C.done = done;
-  C.base = done;
-  // a replica that ran this replay holds a drifted state unless it finished
-  C.clean = (done == C.target && C.err == 0) ? 1 : 0;
+  end_run(C, K, C.base, C.target, C.err, C.err_step);
 }
 
 // Host-ordered update of a replica's target (single thread).
@@ -2426,6 +3048,28 @@ void launch_step(const Tables &T, int grid, int step_in_replay, int mode, int fo
     launch_k_step_r<float>(T, grid, step_in_replay, mode, force_build, only, s, accum, mix);
   if (precisions & PREC_FP64)
     launch_k_step_r<double>(T, grid, step_in_replay, mode, force_build, only, s, accum, mix);
+}
+template <typename R>
+static void *run_kernel(bool accum, bool mix) {
+  if (accum) return mix ? (void *)k_run<R, true, true> : (void *)k_run<R, true, false>;
+  return mix ? (void *)k_run<R, false, true> : (void *)k_run<R, false, false>;
+}
+static void *run_kernel(int precision, bool accum, bool mix) {
+  return precision == PREC_FP64 ? run_kernel<double>(accum, mix) : run_kernel<float>(accum, mix);
+}
+int run_capacity(int precision, bool accum, bool mix, int cus) {
+  int per = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, run_kernel(precision, accum, mix), TILE,
+                                                   0) != hipSuccess)
+    return 0;
+  return per * cus;
+}
+hipError_t launch_run(const Tables &T, int grid, int steps, long long target, bool commit,
+                      int precision, bool accum, bool mix, hipStream_t s) {
+  int c = commit ? 1 : 0;
+  Tables t = T;
+  void *args[] = {&t, &steps, &target, &c};
+  return hipLaunchKernel(run_kernel(precision, accum, mix), dim3(grid), dim3(TILE), args, 0, s);
 }
 void launch_trace(const Tables &T, int K, hipStream_t s) {
   hipLaunchKernelGGL(k_trace, dim3(K, T.nslots), dim3(TILE), 0, s, T, K);
