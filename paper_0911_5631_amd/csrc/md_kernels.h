@@ -32,8 +32,9 @@ void launch_trace(const Tables &T, int K, hipStream_t s);
 void launch_replay_end(const Tables &T, int K, hipStream_t s);
 // target = target; base = done (one replica).
 void launch_set_target(const Tables &T, int slot, long long target, hipStream_t s);
-// Reduce the property partials into the control blocks.
-void launch_props(const Tables &T, int only, hipStream_t s);
+// Reduce the property partials into the control blocks, and copy those to
+// ctl_out (by slot; pinned memory) unless it is null.
+void launch_props(const Tables &T, int only, CtlDev *ctl_out, hipStream_t s);
 // Step (f): scale the held clean velocities to temperature T (after
 // launch_props, which reduces the kinetic energy it scales from).
 void launch_adjust(const Tables &T, int grid, int only, double temperature, hipStream_t s);
@@ -47,6 +48,18 @@ void launch_sort(const Tables &T, int cgrid, int step_in_replay, int mode, int o
 // Cell index of every atom of replica `only` at its held position (storage
 // order) into out[n].
 void launch_cells(const Tables &T, int grid, int only, int32_t *out, hipStream_t s);
+// State of replica r to the host in original order.  launch_invert first (the
+// order of its held state, and its control block to ctl_out, which the device
+// can write: pinned memory); then launch_export for runs of atoms: the arrays
+// of `what` (EXP_*) one after the other into `out` (pinned).
+enum { EXP_POS = 1, EXP_VEL = 2, EXP_FORCE = 4, EXP_U = 8, EXP_W = 16 };
+void launch_invert(const Tables &T, int r, int n, CtlDev *ctl_out, hipStream_t s);
+void launch_export(const Tables &T, int r, int what, int c0, int cnt, double *out, hipStream_t s);
+// Positions and velocities of a run of atoms from the host (`in`, pinned) into
+// a descriptor variant as state `step`; the original order becomes the
+// storage order.
+void launch_import(const SlotDev &S, int64_t step, int c0, int cnt, const double *in,
+                   hipStream_t s);
 // After a sort of the held states: make the sorted variant current.
 void launch_flip(const Tables &T, int only, hipStream_t s);
 // Clear the held state's cell-layer set.

@@ -2855,7 +2855,7 @@ __global__ void k_set_target(Tables T, int slot, long long target) {
 // Fixed-order reduction of the per-tile partials of each replica (one
 // workgroup per replica): thread t takes tiles t, t+256, ... in sequence, then
 // a fixed tree.
-__global__ __launch_bounds__(TILE) void k_props(Tables T, int only) {
+__global__ __launch_bounds__(TILE) void k_props(Tables T, int only, CtlDev *ctl_out) {
   const int r = blockIdx.x;
   if (r >= T.nslots || (only >= 0 && r != only)) return;
   if (slot(T, 2 * r).n <= 0) return;
@@ -2902,7 +2902,14 @@ __global__ __launch_bounds__(TILE) void k_props(Tables T, int only) {
     C.max_m = (int)sh[0][5];
     for (int j = 0; j < NACC; ++j) C.acc_sum[j] = sh[0][6 + j];
   }
+  if (ctl_out != nullptr) {
+    // the control block, to where the host reads it
+    __syncthreads();
+    if (threadIdx.x < sizeof(CtlDev) / 4)
+      ((int32_t *)(ctl_out + r))[threadIdx.x] = ((const int32_t *)&C)[threadIdx.x];
+  }
 }
+static_assert(sizeof(CtlDev) / 4 <= TILE && sizeof(CtlDev) % 4 == 0, "one word per thread");
 
 // Step (f) during equilibration (Secs. 3.1 and 5.1): scale the velocities of a
 // held clean state by one factor so that sum v^2 = 3 (N - 1) T (the centre of
@@ -2997,6 +3004,74 @@ __global__ __launch_bounds__(TILE) void k_cells(Tables T, int only, int32_t *out
   }
 }
 
+// ---------------------------------------------------------------------------
+// state to and from the host
+// ---------------------------------------------------------------------------
+// The storage position of every atom of replica r by original index, into the
+// cell array of the descriptor variant not in use (the next sort overwrites
+// it anyway).
+__device__ __forceinline__ int32_t *inverse_of(const Tables &T, int r) {
+  const CtlDev &C = T.ctl[r];
+  return slot(T, 2 * r + (C.var_ring[mod3(C.done)] ^ 1)).cell;
+}
+__global__ __launch_bounds__(TILE) void k_invert(Tables T, int r, CtlDev *ctl_out) {
+  SlotC &S = slot_held(T, r);
+  const auto inv = gp(inverse_of(T, r));
+  const auto id = gp((const int32_t *)S.id);
+  for (int p = blockIdx.x * TILE + threadIdx.x; p < S.n; p += gridDim.x * TILE)
+    if ((uint32_t)id[p] < (uint32_t)S.n) inv[id[p]] = p;
+  // the control block, to where the host reads it
+  if (blockIdx.x == 0 && threadIdx.x < sizeof(CtlDev) / 4)
+    ((int32_t *)ctl_out)[threadIdx.x] = ((const int32_t *)&T.ctl[r])[threadIdx.x];
+}
+// Atoms c0 .. c0+cnt-1 (original indices) of the arrays in `what` (EXP_*), in
+// the caller's layout, one array after the other, into host memory: the
+// stores are consecutive, so they cross the bus as whole lines, and no copy
+// of the state is made on the device.
+__global__ __launch_bounds__(TILE) void k_export(Tables T, int r, int what, int c0, int cnt,
+                                                 double *out) {
+  SlotC &S = slot_held(T, r);
+  const CtlDev &C = T.ctl[r];
+  const int64_t k = cur_state(C);
+  const int pb = (int)(k & 1), vb = (int)((C.clean ? k + 1 : k) & 1);
+  const auto inv = gp((const int32_t *)inverse_of(T, r));
+  const size_t np = S.npad;
+  const bool f64 = S.fp64 != 0;
+  auto real = [&](const void *a, size_t q) {
+    return f64 ? gp((const double *)a)[q] : (double)gp((const float *)a)[q];
+  };
+  const int n3 = 3 * cnt;
+  for (int kind = 0; kind < 5; ++kind) {
+    if (!(what >> kind & 1)) continue;
+    const bool vec = kind < 3;
+    const int len = vec ? n3 : cnt;
+    for (int e = blockIdx.x * TILE + threadIdx.x; e < len; e += gridDim.x * TILE) {
+      const int j = vec ? e / 3 : e, d = vec ? e - 3 * j : 0;
+      const int p = inv[c0 + j];
+      double v;
+      if (kind == 0) v = gp((const double *)S.P[pb][d])[p];
+      else if (kind == 1) v = gp((const double *)S.V[vb][d])[p];
+      else if (kind == 2) v = real(S.F, d * np + p);
+      else v = real(S.UA, (kind - 3) * np + p);
+      out[e] = v;
+    }
+    out += len;
+  }
+}
+// The reverse for a state at step `step` in descriptor variant `variant`:
+// atoms c0 .. c0+cnt-1 of positions and velocities (host memory, one after
+// the other) in storage order of the original indices.
+__global__ __launch_bounds__(TILE) void k_import(SlotDev S, int step, int c0, int cnt,
+                                                 const double *in) {
+  const int pb = step & 1, vb = pb ^ 1;
+  for (int e = blockIdx.x * TILE + threadIdx.x; e < 3 * cnt; e += gridDim.x * TILE) {
+    const int j = e / 3, d = e - 3 * j;
+    gp(S.P[pb][d])[c0 + j] = in[e];
+    gp(S.V[vb][d])[c0 + j] = in[3 * cnt + e];
+    if (d == 0) gp(S.id)[c0 + j] = c0 + j;
+  }
+}
+
 // Clear the cell-layer set of the held state (before re-binning it).
 __global__ __launch_bounds__(TILE) void k_clear_set(Tables T, int only) {
   const int nct = T.hdr[HDR_NCTILES];
@@ -3080,8 +3155,8 @@ void launch_replay_end(const Tables &T, int K, hipStream_t s) {
 void launch_set_target(const Tables &T, int slot, long long target, hipStream_t s) {
   hipLaunchKernelGGL(k_set_target, dim3(1), dim3(64), 0, s, T, slot, target);
 }
-void launch_props(const Tables &T, int only, hipStream_t s) {
-  hipLaunchKernelGGL(k_props, dim3(T.nslots), dim3(TILE), 0, s, T, only);
+void launch_props(const Tables &T, int only, CtlDev *ctl_out, hipStream_t s) {
+  hipLaunchKernelGGL(k_props, dim3(T.nslots), dim3(TILE), 0, s, T, only, ctl_out);
 }
 void launch_adjust(const Tables &T, int grid, int only, double temperature, hipStream_t s) {
   hipLaunchKernelGGL(k_adjust, dim3(grid), dim3(TILE), 0, s, T, only, temperature);
@@ -3091,6 +3166,22 @@ void launch_insert(const Tables &T, int grid, int wrap_store, int only, hipStrea
 }
 void launch_cells(const Tables &T, int grid, int only, int32_t *out, hipStream_t s) {
   hipLaunchKernelGGL(k_cells, dim3(grid), dim3(TILE), 0, s, T, only, out);
+}
+void launch_invert(const Tables &T, int r, int n, CtlDev *ctl_out, hipStream_t s) {
+  const int g = (n + TILE - 1) / TILE;
+  hipLaunchKernelGGL(k_invert, dim3(g < 2048 ? g : 2048), dim3(TILE), 0, s, T, r, ctl_out);
+}
+void launch_export(const Tables &T, int r, int what, int c0, int cnt, double *out,
+                   hipStream_t s) {
+  const int g = (3 * cnt + TILE - 1) / TILE;
+  hipLaunchKernelGGL(k_export, dim3(g < 1024 ? g : 1024), dim3(TILE), 0, s, T, r, what, c0, cnt,
+                     out);
+}
+void launch_import(const SlotDev &S, int64_t step, int c0, int cnt, const double *in,
+                   hipStream_t s) {
+  const int g = (3 * cnt + TILE - 1) / TILE;
+  hipLaunchKernelGGL(k_import, dim3(g < 1024 ? g : 1024), dim3(TILE), 0, s, S, (int)(step & 1), c0,
+                     cnt, in);
 }
 void launch_flip(const Tables &T, int only, hipStream_t s) {
   hipLaunchKernelGGL(k_flip, dim3((T.nslots + TILE - 1) / TILE), dim3(TILE), 0, s, T, only);
