@@ -139,6 +139,7 @@ struct SlotDev {
   double pk_scale;   // 2^16 / L: units of the packed positions
   uint32_t pk_lim;   // largest squared packed distance of a pair within r_n (0: the
                      // cell-layer rows have no room for packed positions)
+  int32_t run_off, run_n;  // k_run: the replica's seats in a batch
   int32_t pad1;
 };
 
@@ -180,7 +181,10 @@ enum { HDR_NTILES = 0, HDR_NCTILES = 1, HDR_SPLIT = 2, HDR_ORDER = 3 };
 // kernel's workgroups (ORDER_PASSES or ORDER_SLABS, see TileWalk)
 enum { ORDER_PASSES = 0, ORDER_SLABS = 1 };
 constexpr size_t WALK_BYTES = 16 * 64 * 4;  // Tables::walk
-constexpr size_t RUN_BYTES = 88 * 64 * 4;   // Tables::run
+// Tables::run: RUN_HEAD lines of 256 bytes (a batch's seats handed out, its
+// workgroups through), then RUN_LINES for each slot
+constexpr int RUN_HEAD = 2, RUN_LINES = 37;
+constexpr int RUN_SLOTS = 1024;  // a batch with more slots steps in two launches
 
 // Each replica has two descriptors (see SlotDev); CtlDev::var_ring says
 // which one holds a given state.
@@ -195,6 +199,7 @@ struct Tables {
   // zero between launches (the group's last workgroup resets both)
   int32_t *walk;
   int32_t *run;               // k_run's roll call and barriers (zero between launches)
+  const int32_t *run_rep;     // a batch's seat in k_run -> replica
   int32_t nslots;
 };
 

@@ -210,6 +210,8 @@ struct Engine {
   int32_t *d_run = nullptr;     // k_run's roll call and barriers (Tables::run)
   int cus = 0;
   int run_cap[2][2][2] = {};    // k_run's workgroups resident at once, + 1 (0: not asked yet)
+  int32_t *d_run_rep = nullptr; // a batch's seats in k_run (Tables::run_rep)
+  int run_rep_cap = 0, run_seats = 0, run_most = 0;  // room, seats in use, most of one replica
   int tile_cap = 0, ctile_cap = 0;
   CtlDev *h_ctl = nullptr;      // pinned
   SlotDev *h_slots = nullptr;   // pinned [2 * max_slots]
@@ -250,6 +252,7 @@ struct Engine {
     t.hdr = d_hdr;
     t.walk = d_walk;
     t.run = d_run;
+    t.run_rep = d_run_rep;
     t.nslots = max_slots;
     return t;
   }
@@ -361,7 +364,9 @@ md_status engine_init(Engine *e, int max_slots, const md_allocator *a, void *str
   e->d_ctl = (CtlDev *)e->dmalloc(sizeof(CtlDev) * max_slots);
   e->d_hdr = (int32_t *)e->dmalloc(256);
   e->d_walk = (int32_t *)e->dmalloc(WALK_BYTES);
-  e->d_run = (int32_t *)e->dmalloc(RUN_BYTES);
+  const size_t run_bytes =
+      (size_t)(RUN_HEAD + RUN_LINES * (max_slots <= RUN_SLOTS ? max_slots : 0)) * 256;
+  e->d_run = (int32_t *)e->dmalloc(run_bytes);
   if (!e->d_slots || !e->d_ctl || !e->d_hdr || !e->d_walk || !e->d_run) return MD_ERR_OOM;
   err = hipHostMalloc((void **)&e->h_ctl, sizeof(CtlDev) * max_slots, hipHostMallocDefault);
   if (err == hipSuccess)
@@ -374,7 +379,7 @@ md_status engine_init(Engine *e, int max_slots, const md_allocator *a, void *str
   if (err == hipSuccess) err = hipMemsetAsync(e->d_slots, 0, sizeof(SlotDev) * 2 * max_slots, e->work);
   if (err == hipSuccess) err = hipMemsetAsync(e->d_hdr, 0, 256, e->work);
   if (err == hipSuccess) err = hipMemsetAsync(e->d_walk, 0, WALK_BYTES, e->work);
-  if (err == hipSuccess) err = hipMemsetAsync(e->d_run, 0, RUN_BYTES, e->work);
+  if (err == hipSuccess) err = hipMemsetAsync(e->d_run, 0, run_bytes, e->work);
   if (err == hipSuccess) err = hipStreamSynchronize(e->work);
   return err == hipSuccess ? MD_OK : e->fail("engine init", err);
 }
@@ -399,6 +404,7 @@ void engine_free(Engine *e) {
   e->dfree(e->d_hdr);
   e->dfree(e->d_walk);
   e->dfree(e->d_run);
+  e->dfree(e->d_run_rep);
   e->dfree(e->d_tile_rep);
   e->dfree(e->d_ctile_rep);
   if (e->h_ctl) (void)hipHostFree(e->h_ctl);
@@ -496,11 +502,14 @@ void describe(Replica *r) {
   std::swap(e.cell, e.cell_alt);
   std::swap(e.sp, e.sp_alt);
   const int32_t to = r->dev[0].tile_off, co = r->dev[0].ctile_off;
+  const int32_t ro = r->dev[0].run_off, rn = r->dev[0].run_n;
   r->dev[0] = d;
   r->dev[1] = e;
   for (int v = 0; v < 2; ++v) {
     r->dev[v].tile_off = to;
     r->dev[v].ctile_off = co;
+    r->dev[v].run_off = ro;
+    r->dev[v].run_n = rn;
   }
 }
 
@@ -543,14 +552,48 @@ md_status upload_tables(Engine *e) {
     e->d_ctile_rep = (int32_t *)e->dmalloc((size_t)e->ctile_cap * 4);
     if (!e->d_tile_rep || !e->d_ctile_rep) return MD_ERR_OOM;
   }
-  const size_t need = 8 + (size_t)nt + (size_t)nct;
+  // a batch's seats in k_run: one per tile, the largest replicas first (each
+  // takes about as long as any other, and the small ones fill what is left)
+  std::vector<int> order;
+  e->run_seats = e->run_most = 0;
+  if (e->batch) {
+    for (int s = 0; s < e->max_slots; ++s)
+      if (e->rep[s]) order.push_back(s);
+    std::stable_sort(order.begin(), order.end(), [e](int a, int b) {
+      return e->rep[a]->g.ntiles > e->rep[b]->g.ntiles;
+    });
+    for (int s : order) {
+      Replica *r = e->rep[s];
+      for (int v = 0; v < 2; ++v) {
+        r->dev[v].run_off = e->run_seats;
+        r->dev[v].run_n = r->g.ntiles;
+      }
+      e->run_seats += r->g.ntiles;
+      e->run_most = std::max(e->run_most, r->g.ntiles);
+    }
+    if (e->run_seats > e->run_rep_cap) {
+      e->dfree(e->d_run_rep);
+      e->run_rep_cap = std::max(e->run_seats, 2 * e->run_rep_cap);
+      e->d_run_rep = (int32_t *)e->dmalloc((size_t)e->run_rep_cap * 4);
+      if (!e->d_run_rep) {
+        e->run_rep_cap = 0;
+        return MD_ERR_OOM;
+      }
+      // the captured graphs hold the table pointers in their kernel arguments
+      for (auto &kv : e->graphs) (void)hipGraphExecDestroy(kv.second);
+      e->graphs.clear();
+    }
+  }
+  const size_t need = 8 + (size_t)nt + (size_t)nct + (size_t)e->run_seats;
   if (need > e->h_tab_cap) {
     if (e->h_tab) (void)hipHostFree(e->h_tab);
     e->h_tab_cap = std::max(need, 2 * e->h_tab_cap);
     err = hipHostMalloc((void **)&e->h_tab, e->h_tab_cap * 4, hipHostMallocDefault);
     if (err != hipSuccess) return e->fail("pinned tables", err);
   }
-  int32_t *hdr = e->h_tab, *tr = e->h_tab + 8, *ctr = tr + nt;
+  int32_t *hdr = e->h_tab, *tr = e->h_tab + 8, *ctr = tr + nt, *rr = ctr + nct;
+  for (int s : order)
+    for (int k = 0; k < e->rep[s]->g.ntiles; ++k) rr[e->rep[s]->dev[0].run_off + k] = s;
   memset(hdr, 0, 32);
   hdr[HDR_NTILES] = nt;
   hdr[HDR_NCTILES] = nct;
@@ -581,6 +624,8 @@ md_status upload_tables(Engine *e) {
     err = hipMemcpyAsync(e->d_tile_rep, tr, (size_t)nt * 4, hipMemcpyHostToDevice, e->work);
   if (err == hipSuccess && nct)
     err = hipMemcpyAsync(e->d_ctile_rep, ctr, (size_t)nct * 4, hipMemcpyHostToDevice, e->work);
+  if (err == hipSuccess && e->run_seats)
+    err = hipMemcpyAsync(e->d_run_rep, rr, (size_t)e->run_seats * 4, hipMemcpyHostToDevice, e->work);
   if (err == hipSuccess)
     err = hipMemcpyAsync(e->d_slots, e->h_slots, sizeof(SlotDev) * 2 * e->max_slots,
                          hipMemcpyHostToDevice, e->work);
@@ -904,20 +949,29 @@ hipGraphExec_t step_graph(Engine *e, int k) {
 int run_grid(const Engine *e) { return (e->rep[0]->g.ntiles + 7) / 8 * 8; }
 
 // Whether the steps of this engine are taken by k_run, several per launch: a
-// single system whose tiles are all resident at once (1 024 tiles, 262 144
-// atoms; a mixture 768), unless its launches are timed one by one or were
-// given grids of their own.  At N = 256 000 (1 000 tiles) a step takes 26.6 us
-// this way and 30.7 in two launches, at N = 864 12.2 and 16.7; beyond the limit
-// each workgroup would walk several tiles with device-scope reads, where
-// k_step's tiles share their neighbours through the XCD's L2.
-bool use_run(Engine *e) {
-  if (e->batch || e->profiling || !e->rep[0] || e->cus <= 0) return false;
-  if (e->grid_req > 0 || e->cgrid_req > 0 || e->split_req > 0) return false;
-  if (e->prec != PREC_FP32 && e->prec != PREC_FP64) return false;
+// single system, or every replica of a batch, whose tiles are all resident at
+// once (1 024 tiles, 262 144 atoms; a mixture 768), unless its launches are
+// timed one by one or were given grids of their own.  At N = 256 000 (1 000
+// tiles) a step takes 24.7 us this way and 30.1 in two launches, at N = 864
+// 11.5 and 17.3; 48 replicas of 864 to 32 000 atoms 64 and 108, 2 of them 15
+// and 40 (in launches every step waits for the slowest tile of any replica
+// that rebuilds); 256 replicas, 12 rounds of seats, 277 and 284.  Beyond the
+// limit each workgroup would walk several tiles with device-scope reads,
+// where k_step's tiles share their neighbours through the XCD's L2.
+int run_capacity_of(Engine *e, int prec) {
   const bool acc = e->accum || e->trace;
-  int &cap = e->run_cap[e->prec == PREC_FP64][acc][e->mix];
-  if (cap == 0) cap = 1 + run_capacity(e->prec, acc, e->mix, e->cus);
-  return run_grid(e) < cap;
+  int &cap = e->run_cap[prec == PREC_FP64][acc][e->mix];
+  if (cap == 0) cap = 1 + run_capacity(prec, acc, e->mix, e->cus);
+  return cap - 1;
+}
+bool use_run(Engine *e) {
+  if (e->profiling || e->cus <= 0 || e->max_slots > RUN_SLOTS) return false;
+  if (e->grid_req > 0 || e->cgrid_req > 0 || e->split_req > 0) return false;
+  const int most = e->batch ? e->run_most : e->rep[0] ? run_grid(e) : 0;
+  if (most == 0) return false;
+  for (int p : {PREC_FP32, PREC_FP64})
+    if ((e->prec & p) && most > run_capacity_of(e, p)) return false;
+  return true;
 }
 
 md_status prof_collect(Engine *e, int set) {
@@ -982,7 +1036,7 @@ md_status run_steps(Engine *e, int64_t from, int64_t to) {
     const Tables T = e->tables();
     while (pos < to) {
       const int k = (int)std::min<int64_t>(e->trace ? MAX_REPLAY : RUN_STEPS, to - pos);
-      const hipError_t err = launch_run(T, run_grid(e), k, to, !e->trace, e->prec,
+      const hipError_t err = launch_run(T, run_grid(e), k, to, !e->trace, 0, e->prec,
                                         e->accum || e->trace, e->mix, e->work);
       if (err != hipSuccess) return e->fail("run launch", err);
       if (e->trace) {
@@ -2091,6 +2145,22 @@ md_status md_batch_run(md_batch *b) {
   Visit v(e);
   md_status st = v.enter();
   if (st != MD_OK) return st;
+  if (use_run(e)) {
+    const Tables T = e->tables();
+    for (int p : {PREC_FP32, PREC_FP64}) {
+      if (!(e->prec & p)) continue;
+      const hipError_t err = launch_run(T, std::min(e->run_seats, run_capacity_of(e, p)),
+                                        e->steps_per_run, -1, !e->trace, e->run_seats, p, e->trace,
+                                        e->mix, e->work);
+      if (err != hipSuccess) return e->fail("run launch", err);
+    }
+    if (e->trace) {
+      launch_trace(T, e->steps_per_run, e->work);
+      launch_replay_end(T, e->steps_per_run, e->work);
+    }
+    if ((st = e->check("run launches")) != MD_OK) return st;
+    return v.leave();
+  }
   launch_kick(e->tables(), e->grid, e->work);
   if ((st = e->check("kick")) != MD_OK) return st;
   if ((st = replay(e, e->steps_per_run)) != MD_OK) return st;

@@ -18,12 +18,13 @@ enum { PREC_FP32 = 1, PREC_FP64 = 2 };
 // replicas have several species.
 void launch_step(const Tables &T, int grid, int step_in_replay, int mode, int force_build,
                  int only, int precisions, hipStream_t s, bool accum = false, bool mix = false);
-// Several steps of the one replica of T in one launch (k_run): the first half
-// kick where the state is clean, then up to `steps` steps towards target, and
-// the step counters when commit is set.  grid: 8 ceil(tiles / 8), at most
-// run_capacity() (workgroups of the kernel resident at once).
+// Several steps of every replica of T in one launch (k_run): the first half
+// kick where the state is clean, then up to `steps` steps towards target (< 0:
+// each replica's own), and the step counters when commit is set.  grid: for a
+// system alone 8 ceil(tiles / 8); for a batch the workgroups that take its
+// `seats`; at most run_capacity() (workgroups of the kernel resident at once).
 hipError_t launch_run(const Tables &T, int grid, int steps, long long target, bool commit,
-                      int precision, bool accum, bool mix, hipStream_t s);
+                      int seats, int precision, bool accum, bool mix, hipStream_t s);
 int run_capacity(int precision, bool accum, bool mix, int cus);
 // Traced replicas: the properties of the replay's K steps into their trace
 // rings (before launch_replay_end).

@@ -255,6 +255,7 @@ __device__ __forceinline__ bool check_atom(SlotC &S, CtlDev &C, double x, double
 // counter (atomic), the row entry, or the set's overflow list beyond hcap.
 // The sort of a rebuild step reads the rows; the cell each atom lands in
 // there is written by the sort itself.
+template <bool COH>
 __device__ __forceinline__ void bin_atom(SlotC &S, CtlDev &C, int set, int i, double x, double y,
                          double z, int64_t step) {
   // Called by a prefix of the lanes of a wave (the active atoms of a tile).
@@ -290,12 +291,12 @@ __device__ __forceinline__ void bin_atom(SlotC &S, CtlDev &C, int set, int i, do
   const int tnext = tafter ? __ffsll((long long)tafter) - 1 : na;
   if (tlead) atomicAdd(&S.tcnt[set][ct], tnext - lane);
   if (slot < S.hcap) {
-    gp(S.H[set])[(size_t)c * S.hcap + slot] = i;
+    st<COH>(&gp(S.H[set])[(size_t)c * S.hcap + slot], i);
   } else {
     const int o = atomicAdd(&S.ovf_n[set], 1);
     if (o < OVF_CAP) {
-      S.ovf[set][2 * o] = c;
-      S.ovf[set][2 * o + 1] = i;
+      st<COH>(&gp(S.ovf[set])[2 * o], c);
+      st<COH>(&gp(S.ovf[set])[2 * o + 1], i);
     } else {
       latch_error(C, ERR_CELL, step);
     }
@@ -324,7 +325,7 @@ __device__ __forceinline__ void sort8(int (&v)[8]) {
 // depends on atomic timing, so it is not used).  Up to eight atoms held in
 // the row are ordered with a sorting network; larger or overflowing cells
 // take repeated minimum searches over the row and the set's overflow list.
-template <class Visit>
+template <bool COH, class Visit>
 __device__ __forceinline__ void visit_cell(SlotC &S, int set, int c, int cnt,
                                            Visit &&visit) {
   const int32_t *__restrict__ row = S.H[set] + (size_t)c * S.hcap;
@@ -332,7 +333,7 @@ __device__ __forceinline__ void visit_cell(SlotC &S, int set, int c, int cnt,
   if (cnt <= 8 && inrow == cnt) {
     int v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = e < cnt ? gp(row)[e] : INT_MAX;
+    for (int e = 0; e < 8; ++e) v[e] = e < cnt ? ld<COH>(&gp(row)[e]) : INT_MAX;
     sort8(v);
 #pragma unroll
     for (int e = 0; e < 8; ++e)
@@ -343,15 +344,15 @@ __device__ __forceinline__ void visit_cell(SlotC &S, int set, int c, int cnt,
   for (int r = 0; r < cnt; ++r) {
     int best = INT_MAX;
     for (int e = 0; e < inrow; ++e) {
-      const int v = gp(row)[e];
+      const int v = ld<COH>(&gp(row)[e]);
       best = (v > last && v < best) ? v : best;
     }
     if (cnt > inrow) {
-      const int no = min(S.ovf_n[set], OVF_CAP);
-      const int32_t *__restrict__ ov = S.ovf[set];
+      const int no = min(ld<COH>(&gp((const int32_t *)S.ovf_n)[set]), OVF_CAP);
+      const gcint ov = gp((const int32_t *)S.ovf[set]);
       for (int e = 0; e < no; ++e)
-        if (ov[2 * e] == c) {
-          const int v = ov[2 * e + 1];
+        if (ld<COH>(&ov[2 * e]) == c) {
+          const int v = ld<COH>(&ov[2 * e + 1]);
           best = (v > last && v < best) ? v : best;
         }
     }
@@ -449,12 +450,12 @@ __device__ __forceinline__ void kick_tile(SlotC &S, CtlDev &C, int lt, int64_t k
   double xn[3];
   for (int a = 0; a < 3; ++a) {
     const double v = gp(S.V[vb][a])[i] + S.hdt * f[a];
-    gp(S.V[vb][a])[i] = v;
+    st<COH>(&gp(S.V[vb][a])[i], v);
     xn[a] = gp(S.P[pb][a])[i] + S.dt * v;
     st<COH>(&gp(S.P[pb ^ 1][a])[i], xn[a]);
   }
   if (bin)
-    bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
+    bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
   else
     check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
 }
@@ -537,6 +538,7 @@ struct SortRun {
 // Share sp of nsp of cell tile t of replica r at step k (the sorts of a step:
 // mode MODE_STEP, v(k-1/2) is carried; of the held state: v(k)): from
 // descriptor S into D, or in place without reordering (!reo).
+template <bool COH>
 __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t k, int mode,
                                           bool reo, int t, int sp, int nsp, int r, SortRun &run,
                                           SortLds &lds) {
@@ -565,18 +567,18 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
     for (; q + 7 * TILE < lt; q += 8 * TILE) {
       int p8[8];
 #pragma unroll
-      for (int u8 = 0; u8 < 8; ++u8) p8[u8] = TC[q + u8 * TILE];
+      for (int u8 = 0; u8 < 8; ++u8) p8[u8] = ld<COH>(&TC[q + u8 * TILE]);
 #pragma unroll
       for (int u8 = 0; u8 < 8; ++u8) pre += p8[u8];
     }
-    for (; q < lt; q += TILE) pre += TC[q];
+    for (; q < lt; q += TILE) pre += ld<COH>(&TC[q]);
   }
   for (int o = 32; o > 0; o >>= 1) pre += __shfl_xor(pre, o, 64);
   if (l == 0) lds.s_red[w] = pre;
 
   // workgroup exclusive scan of one cell count per thread
   const int c = lt * CTILE + tid;
-  const int cnt = c < S.ncell ? gp(S.cnt[set])[c] : 0;
+  const int cnt = c < S.ncell ? ld<COH>(&gp((const int32_t *)S.cnt[set])[c]) : 0;
   int incl = cnt;
   for (int o = 1; o < 64; o <<= 1) {
     const int y = __shfl_up(incl, o, 64);
@@ -592,7 +594,7 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
   const int base = before + incl - cnt;
   if (sp == 0) {
     if (l == 0 && wmax > C.max_h) atomicMax(&C.max_h, wmax);
-    if (c <= S.ncell) gp(S.cs)[c] = base;  // c == ncell: the total, n
+    if (c <= S.ncell) st<COH>(&gp(S.cs)[c], base);  // c == ncell: the total, n
   }
 
   // Every atom goes to base of its cell + its rank by current index.  This
@@ -626,14 +628,14 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
         const int32_t *row = S.H[set] + (size_t)c * S.hcap;
         int v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = e < cnt ? gp(row)[e] : INT_MAX;
+        for (int e = 0; e < 8; ++e) v[e] = e < cnt ? ld<COH>(&gp(row)[e]) : INT_MAX;
         sort8(v);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           if (e < cnt) list(base + e, v[e], tid);
       } else {
         // a cell that spilled into the overflow list: repeated minimum searches
-        visit_cell(S, set, c, cnt, [&](int atom, int q) { list(base + q, atom, tid); });
+        visit_cell<COH>(S, set, c, cnt, [&](int atom, int q) { list(base + q, atom, tid); });
       }
     }
     // larger cells whose members all sit in their rows, by the whole
@@ -675,9 +677,9 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
         const int cj = lds.s_bc[lo];
         const int cntj = (lo + 1 < nb ? lds.s_bp[lo + 1] : B) - lds.s_bp[lo];
         const auto row = gp((const int32_t *)S.H[set]) + (size_t)cj * S.hcap;
-        const int v = row[q - lds.s_bp[lo]];
+        const int v = ld<COH>(&row[q - lds.s_bp[lo]]);
         int rank = 0;
-        for (int f = 0; f < cntj; ++f) rank += row[f] < v ? 1 : 0;
+        for (int f = 0; f < cntj; ++f) rank += ld<COH>(&row[f]) < v ? 1 : 0;
         list(lds.s_bb[lo] + rank, v, cj - lt * CTILE);
       }
       __syncthreads();
@@ -698,10 +700,10 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
         for (int u = 0; u < 4; ++u) {
           const int q = at[u];
           if (q < 0) continue;
-          gp(S.perm)[p0 + u * TILE] = q;
-          gp(S.cell)[q] = cc[u];
+          st<COH>(&gp(S.perm)[p0 + u * TILE], q);
+          st<COH>(&gp(S.cell)[q], cc[u]);
 #pragma unroll
-          for (int d = 0; d < 3; ++d) gp(S.P[pb][d])[q] = wrap1(gp(S.P[pb][d])[q], L, halfL);
+          for (int d = 0; d < 3; ++d) st<COH>(&gp(S.P[pb][d])[q], wrap1(ld<COH>(&gp((const double *)S.P[pb][d])[q]), L, halfL));
         }
         continue;
       }
@@ -712,11 +714,11 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
         const int q = max(at[u], 0);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          pv[u][d] = gp(S.P[pb][d])[q];
-          pv[u][3 + d] = gp(S.V[vb][d])[q];
+          pv[u][d] = ld<COH>(&gp((const double *)S.P[pb][d])[q]);
+          pv[u][3 + d] = ld<COH>(&gp((const double *)S.V[vb][d])[q]);
         }
-        idv[u] = gp(S.id)[q];
-        spv[u] = mixsp ? gp(S.sp)[q] : 0;
+        idv[u] = ld<COH>(&gp((const int32_t *)S.id)[q]);
+        spv[u] = mixsp ? ld<COH>(&gp((const int32_t *)S.sp)[q]) : 0;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -726,13 +728,13 @@ __device__ __forceinline__ void sort_unit(SlotC &S, SlotC &D, CtlDev &C, int64_t
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           x[d] = wrap1(pv[u][d], L, halfL);
-          gp(D.P[pb][d])[p] = x[d];
-          gp(D.V[vb][d])[p] = pv[u][3 + d];
+          st<COH>(&gp(D.P[pb][d])[p], x[d]);
+          st<COH>(&gp(D.V[vb][d])[p], pv[u][3 + d]);
         }
-        if (packed) PK[p] = pk_of(S, x[0], x[1], x[2]);
-        gp(D.id)[p] = idv[u];
-        gp(D.cell)[p] = cc[u];
-        if (mixsp) gp(D.sp)[p] = spv[u];
+        if (packed) st<COH>(&PK[p], pk_of(S, x[0], x[1], x[2]));
+        st<COH>(&gp(D.id)[p], idv[u]);
+        st<COH>(&gp(D.cell)[p], cc[u]);
+        if (mixsp) st<COH>(&gp(D.sp)[p], spv[u]);
       }
     }
     __syncthreads();
@@ -866,7 +868,7 @@ __global__ __launch_bounds__(TILE, 4) void k_sort(Tables T, int s, int mode, int
         continue;
       }
     }
-    sort_unit(slot(T, 2 * r + var), slot(T, 2 * r + (var ^ 1)), C, k, mode, reo, t, sp, nsp, r,
+    sort_unit<false>(slot(T, 2 * r + var), slot(T, 2 * r + (var ^ 1)), C, k, mode, reo, t, sp, nsp, r,
               run, lds);
   }
 }
@@ -1208,6 +1210,7 @@ __device__ __forceinline__ void make_window(SlotC &S, int lt, Window &w, int *sc
   __syncthreads();
 }
 
+template <bool COH>
 __device__ __forceinline__ void stage_species(const int *wt, gcint SP, int8_t *ssp) {
   const int tid = tid_here(), nint = wt[0];
   if (nint <= 0) return;
@@ -1218,7 +1221,7 @@ __device__ __forceinline__ void stage_species(const int *wt, gcint SP, int8_t *s
       ++q;
       end = wt[3 * q + 3] + wt[3 * q + 2];
     }
-    ssp[sl] = (int8_t)SP[wt[3 * q + 1] + (sl - wt[3 * q + 3])];
+    ssp[sl] = (int8_t)ld<COH>(&SP[wt[3 * q + 1] + (sl - wt[3 * q + 3])]);
   }
 }
 
@@ -1261,7 +1264,7 @@ __device__ __forceinline__ void stage_window(const int *wt, gcdouble X, gcdouble
   }
   // the species bytes through registers (after the coordinates' loads have
   // gone out)
-  if constexpr (MIX) stage_species(wt, SP, ssp);
+  if constexpr (MIX) stage_species<COH>(wt, SP, ssp);
 }
 
 // Storage bounds of neighbour row q (dz = q / 3 - 1, dy = q % 3 - 1) of an
@@ -1368,11 +1371,11 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
         z = sz[j + d];
         if (MIX) sj = ssp[j + d];
       } else {
-        if (noreo) js = PERM[j];
+        if (noreo) js = ld<COH>(&PERM[j]);
         x = ld<COH>(&X[js]);
         y = ld<COH>(&Y[js]);
         z = ld<COH>(&Z[js]);
-        if (MIX) sj = SP[js];
+        if (MIX) sj = ld<COH>(&SP[js]);
       }
     };
     auto separation = [&](double x, double y, double z, bool isw, double &dx, double &dy,
@@ -1627,7 +1630,7 @@ __device__ __forceinline__ void entry_pos(uint32_t e, gcdouble X, gcdouble Y, gc
     xj = ld<COH>(&X[idx]);
     yj = ld<COH>(&Y[idx]);
     zj = ld<COH>(&Z[idx]);
-    if (MIX) sj = SP[idx];
+    if (MIX) sj = ld<COH>(&SP[idx]);
   } else {
     xj = sx[idx];
     yj = sy[idx];
@@ -1801,12 +1804,17 @@ __device__ __forceinline__ void finish_tile(SlotC &S, CtlDev &C, Lds &lds, int l
             __builtin_nontemporal_store(xn[q], &gp(S.P[pb ^ 1][q])[i]);
         }
         if (bin_next)
-          bin_atom(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
+          bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
         else
           check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
       }
       if (put_v)
-        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(v[q], &gp(S.V[pb ^ 1][q])[i]);
+        for (int q = 0; q < 3; ++q) {
+          if (COH)
+            st<true>(&gp(S.V[pb ^ 1][q])[i], v[q]);
+          else
+            __builtin_nontemporal_store(v[q], &gp(S.V[pb ^ 1][q])[i]);
+        }
     }
     if (mode != MODE_STEP || last) {
       auto F = gp((R *)S.F);
@@ -1963,14 +1971,16 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, StepLds<MIX> &lds
     yi = ld<COH>(&Y[i]);
     zi = ld<COH>(&Z[i]);
     if (force)
-      for (int q = 0; q < 3; ++q) v[q] = __builtin_nontemporal_load(&gp(S.V[vb][q])[i]);
+      for (int q = 0; q < 3; ++q)
+        v[q] = COH ? ld<COH>(&gp((const double *)S.V[vb][q])[i])
+                   : __builtin_nontemporal_load(&gp(S.V[vb][q])[i]);
     if (list) {
       m = __builtin_nontemporal_load(&gp(S.m)[i]);
 #pragma unroll
       for (int u = 0; u < NE; ++u)
         e[u] = u < S.mcap ? (uint32_t)__builtin_nontemporal_load(&Wc[(size_t)u * np]) : 0u;
     } else if (cells) {
-      ci = gp(S.cell)[i];
+      ci = ld<COH>(&gp((const int32_t *)S.cell)[i]);
     }
   }
 
@@ -1984,7 +1994,7 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, StepLds<MIX> &lds
     constexpr int NT = (int)(sizeof(PairTab) / sizeof(double));
     if (tid < NT)
       ((double *)&lds.tab)[tid] = gp((const double *)S.tab)[tid];
-    if (act) spi = SP[i];
+    if (act) spi = ld<COH>(&SP[i]);
   }
   // a cell step: the bounds of the first neighbour row of the traversal go
   // out before the window is built (wave 0 builds it; the others wait)
@@ -2046,7 +2056,7 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, StepLds<MIX> &lds
         gx[u] = ld<COH>(&X[idx]);
         gy[u] = ld<COH>(&Y[idx]);
         gz[u] = ld<COH>(&Z[idx]);
-        if (MIX) gs[u] = SP[idx];
+        if (MIX) gs[u] = ld<COH>(&SP[idx]);
       }
     }
   }
@@ -2201,15 +2211,15 @@ __device__ __forceinline__ void own_load(SlotC &S, StepLds<MIX> &lds, int lt, in
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       o.x[q] = ld<true>(&gp((const double *)S.P[pb][q])[i]);
-      o.v[q] = gp((const double *)S.V[pb][q])[i];
+      o.v[q] = ld<true>(&gp((const double *)S.V[pb][q])[i]);
     }
     o.m = gp((const int32_t *)S.m)[i];
-    if (MIX) o.sp = gp((const int32_t *)S.sp)[i];
+    if (MIX) o.sp = ld<true>(&gp((const int32_t *)S.sp)[i]);
 #pragma unroll
     for (int u = 0; u < Own<R>::NR; ++u) o.e[u] = u < S.mcap ? (uint32_t)W[(size_t)u * np] : 0u;
   }
   __syncthreads();
-  if constexpr (MIX) stage_species(lds.win.wt, gp((const int32_t *)S.sp), lds.ssp);
+  if constexpr (MIX) stage_species<true>(lds.win.wt, gp((const int32_t *)S.sp), lds.ssp);
 }
 // A list step of the held tile (the list path of step_tile, entry for entry).
 template <typename R, bool ACC, bool MIX>
@@ -2258,7 +2268,7 @@ __device__ __forceinline__ void own_step(SlotC &S, CtlDev &C, StepLds<MIX> &lds,
       }
     } else {
       // its list overflowed: over the 27 cells of its cell at the last sort
-      traverse_sorted<R, MIX, true>(S, i, gp(S.cell)[i], X, Y, Z, lds.win, sx, sy, sz, o.x[0],
+      traverse_sorted<R, MIX, true>(S, i, ld<true>(&gp((const int32_t *)S.cell)[i]), X, Y, Z, lds.win, sx, sy, sz, o.x[0],
                                     o.x[1], o.x[2], false, true, energy, a, ssp, SP, o.sp, tab,
                                     unord, true);
     }
@@ -2272,7 +2282,7 @@ __device__ __forceinline__ void own_store(SlotC &S, int lt, int64_t k, const Own
   const int i = lt * TILE + tid_here();
   if (i < S.n)
 #pragma unroll
-    for (int q = 0; q < 3; ++q) gp(S.V[k & 1][q])[i] = o.v[q];
+    for (int q = 0; q < 3; ++q) st<true>(&gp(S.V[k & 1][q])[i], o.v[q]);
 }
 
 // ACC: every step of this launch also adds its properties to the block sums
@@ -2457,27 +2467,29 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 // with fewer participants than tiles each steps several.  (The spin bound of
 // the barriers is a backstop: it latches ERR_STALL.)
 //
-// What is shared: positions and the cell counters cross between workgroups
-// with device-scope loads and stores (ld, st), so an ordinary step needs no
-// cache maintenance; the barriers around a sort, whose plain stores are read
-// by other workgroups, are full release/acquire fences.  A tile's velocities,
-// list and window are only touched by its own workgroup between sorts.
+// What is shared: everything that another workgroup may read in the same
+// launch is stored device-scope (st) and read so (ld), past the caches that
+// only one XCD or CU sees.  The exceptions are the packed positions and
+// cell_start, which a build reads again and again: they are read plainly,
+// behind a barrier that invalidates the caches.  A tile's list and window are
+// only touched by its own workgroup.  (Plain stores with one write-back per
+// XCD, by the last workgroup to arrive there, missed stores of other waves
+// once in some 10^5 rebuilds.)
 constexpr long long ROLL_TICKS = 10000;  // 100 us of the 100 MHz clock
+// in a batch a replica's last workgroup may come when another's replica is
+// through: 64 steps of 13-60 us
+constexpr long long ROLL_TICKS_BATCH = 500000;  // 5 ms
 constexpr int RUN_SPINS = 1 << 22;
-// Words of Tables::run, each on its own 256-byte line; zero between launches.
+// A replica's words of Tables::run, each on its own 256-byte line; zero between
+// launches.
 enum { RUN_GROUPS = 32, RUN_ROOT = 32, RUN_EPOCH = 33, RUN_ARRIVE = 34, RUN_STATE = 35,
-       RUN_EXIT = 36, RUN_XROOT = 37, RUN_XEPOCH = 38, RUN_XCNT = 40, RUN_XARR = 56, RUN_XFLAG = 72,
-       RUN_LINES = 88 };
-constexpr int MAX_XCD = 16;
-static_assert(RUN_LINES * 256 <= RUN_BYTES, "Tables::run");
+       RUN_EXIT = 36, RUN_END = 37 };
+static_assert(RUN_END <= RUN_LINES, "Tables::run");
 
-// What a participant knows of the others: its place among n, its XCD, how
-// many participants share it (0: not everybody is present, so nobody has
-// counted them) and how many XCDs there are.
+// A participant's place among n (epoch: barriers passed).
 struct RunSeat {
   int32_t *w;
-  int rank, n, xcd, inx, nx;
-  int epoch, xepoch;  // barriers and fences passed
+  int rank, n, epoch;
 };
 // The maximum speed of a ring entry and the error word as of a barrier.
 struct RunOut {
@@ -2494,54 +2506,32 @@ __device__ __forceinline__ bool run_wait(int32_t *f, int v) {
 
 // The grid barrier.  Arrivals are counted in 32 groups, then over the groups:
 // 1 000 workgroups on one counter took 12.7 us, in 32 groups 2.0.
-// full: everything stored before it is seen after it.  A write-back or an
-// invalidation acts on a whole XCD's L2, so one workgroup per XCD, the last
-// there to arrive, writes it back, and invalidates it when all XCDs have; the
-// others then only drop their CU's L1.  (By every wave the two fences took
-// 70 us and 45 us at 1 000 workgroups.)
+// drop: plain loads after it see what was stored (device-scope) before it:
+// the caches of the CU and of its XCD are invalidated, by one wave for its
+// workgroup.
 // The maximum speed of ring entry e (e < 0: none) and the error word are left
 // in `out`.
-__device__ __forceinline__ void run_barrier(RunSeat &p, bool full, SlotC &S0, CtlDev &C, int e,
+__device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, SlotC &S0, CtlDev &C, int e,
                                             RunOut &out) {
   constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
   int32_t *w = p.w;
-  const bool all = p.inx > 0;
-  if (full && !all) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have arrived
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's device-scope stores have arrived
   __syncthreads();
-  if (full && all)
-    ++p.xepoch;
-  else
-    ++p.epoch;
+  ++p.epoch;
   if (threadIdx.x < 64) {
     bool ok = true;
     if (threadIdx.x == 0) {
-      if (full && all) {
-        if (__hip_atomic_fetch_add(&w[64 * (RUN_XARR + p.xcd)], 1, __ATOMIC_RELAXED, AG) ==
-            p.xepoch * p.inx - 1) {
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-          if (__hip_atomic_fetch_add(&w[64 * RUN_XROOT], 1, __ATOMIC_RELAXED, AG) ==
-              p.xepoch * p.nx - 1)
-            __hip_atomic_store(&w[64 * RUN_XEPOCH], p.xepoch, __ATOMIC_RELAXED, AG);
-          ok = run_wait(&w[64 * RUN_XEPOCH], p.xepoch);
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-          __hip_atomic_store(&w[64 * (RUN_XFLAG + p.xcd)], p.xepoch, __ATOMIC_RELAXED, AG);
-        } else {
-          ok = run_wait(&w[64 * (RUN_XFLAG + p.xcd)], p.xepoch);
-        }
-      } else {
-        const int g = p.rank & (RUN_GROUPS - 1), in = (p.n - g + RUN_GROUPS - 1) / RUN_GROUPS;
-        const int ng = p.n < RUN_GROUPS ? p.n : RUN_GROUPS;
-        if (__hip_atomic_fetch_add(&w[64 * g], 1, __ATOMIC_RELAXED, AG) == p.epoch * in - 1 &&
-            __hip_atomic_fetch_add(&w[64 * RUN_ROOT], 1, __ATOMIC_RELAXED, AG) ==
-                p.epoch * ng - 1)
-          __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch, __ATOMIC_RELAXED, AG);
-        ok = run_wait(&w[64 * RUN_EPOCH], p.epoch);
-      }
+      const int g = p.rank & (RUN_GROUPS - 1), in = (p.n - g + RUN_GROUPS - 1) / RUN_GROUPS;
+      const int ng = p.n < RUN_GROUPS ? p.n : RUN_GROUPS;
+      if (__hip_atomic_fetch_add(&w[64 * g], 1, __ATOMIC_RELAXED, AG) == p.epoch * in - 1 &&
+          __hip_atomic_fetch_add(&w[64 * RUN_ROOT], 1, __ATOMIC_RELAXED, AG) == p.epoch * ng - 1)
+        __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch, __ATOMIC_RELAXED, AG);
+      ok = run_wait(&w[64 * RUN_EPOCH], p.epoch);
     }
     if (!ok) atomicOr(&C.err, ERR_STALL);
     __builtin_amdgcn_s_waitcnt(0);
-    if (full && all) asm volatile("buffer_inv sc0" ::: "memory");  // this CU's L1
+    // (the loads below come back after the invalidation)
+    if (drop) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     unsigned long long v = 0;
     if (e >= 0 && threadIdx.x < VSPREAD)
       v = __hip_atomic_load(&S0.vring[(e * VSPREAD + threadIdx.x) * 16], __ATOMIC_RELAXED, AG);
@@ -2553,29 +2543,31 @@ __device__ __forceinline__ void run_barrier(RunSeat &p, bool full, SlotC &S0, Ct
     }
   }
   __syncthreads();
-  if (full && !all) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-// Steps done + 1 .. min(done + steps, target) of the one replica of T.
-// commit: also the step counters (a traced replica's are advanced after its
-// trace has been reduced).
+// One workgroup's part in steps done + 1 .. min(done + steps, target) of
+// replica r, which `size` workgroups (this one `seat` of them) come to take.
+// A target below zero: the one in the control block.  commit: also the step
+// counters (a traced replica's are advanced after its trace has been
+// reduced).  solo: the launch is this replica's alone.
 template <typename R, bool ACC, bool MIX>
-__global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, long long target,
-                                                         int commit) {
+__device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, int r, int seat,
+                                            int size, bool solo, int steps, long long to,
+                                            int commit) {
   constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
-  __shared__ StepLds<MIX> lds;
   // (every thread has read `out` and the roll call before a tile's first
   // barrier, after which the tile writes these words)
   RunOut &out = *(RunOut *)lds.sh;
   int &s_rank = ((int *)lds.sv)[0], &s_n = ((int *)lds.sv)[1];
   static_assert(sizeof(SortLds) <= sizeof(lds.sx), "the sort's LDS shares the window's");
   SortLds &slds = *(SortLds *)lds.sx;
-  int32_t *w = T.run;
-  CtlDev &C = T.ctl[0];
-  SlotC &S0 = slot(T, 0);
+  int32_t *w = T.run + 64 * (RUN_HEAD + RUN_LINES * r);
+  CtlDev &C = T.ctl[r];
+  SlotC &S0 = slot(T, 2 * r);
   // the control words as earlier launches left them (this launch writes them
   // only after the roll call)
-  const auto &C0 = *cview(T.ctl);
+  const auto &C0 = *cview(T.ctl + r);
+  const int64_t target = to < 0 ? C0.target : (int64_t)to;
   const int64_t done = C0.done, force_step = C0.force_step, bins_step = C0.bins_step;
   const int64_t end = done + steps < target ? done + steps : target;
   const bool clean = C0.clean != 0, cell_only = S0.cell_only != 0;
@@ -2588,24 +2580,20 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
   const bool idle = C0.err != 0 || done >= end;
   // (read here: a workgroup that comes after the others have gone on may find
   // other words, and takes no part)
-  asm volatile("" ::"s"(done), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean));
+  asm volatile("" ::"s"(done), "s"(target), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean));
   // roll call
-  // (XCC_ID, hardware register 20, 4 bits)
   RunSeat me;
   me.w = w;
-  me.epoch = me.xepoch = 0;
-  me.xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (MAX_XCD - 1);
+  me.epoch = 0;
   if (threadIdx.x == 0) {
-    (void)__hip_atomic_fetch_add(&w[64 * (RUN_XCNT + me.xcd)], 1, __ATOMIC_RELAXED, AG);
-    __builtin_amdgcn_s_waitcnt(0);  // (counted there before it is counted present)
     const int rank = __hip_atomic_fetch_add(&w[64 * RUN_ARRIVE], 1, __ATOMIC_RELAXED, AG);
     int n = 0, zero = 0;
-    if (rank == (int)gridDim.x - 1)
+    if (rank == size - 1)
       __hip_atomic_compare_exchange_strong(&w[64 * RUN_STATE], &zero, rank + 1, __ATOMIC_RELAXED,
                                            __ATOMIC_RELAXED, AG);
     const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
     while ((n = __hip_atomic_load(&w[64 * RUN_STATE], __ATOMIC_RELAXED, AG)) == 0) {
-      if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > ROLL_TICKS) {
+      if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > (solo ? ROLL_TICKS : ROLL_TICKS_BATCH)) {
         zero = 0;
         __hip_atomic_compare_exchange_strong(
             &w[64 * RUN_STATE], &zero,
@@ -2619,25 +2607,21 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
   }
   __syncthreads();
   const int n = __builtin_amdgcn_readfirstlane(s_n);
-  const bool all = n == (int)gridDim.x;
+  const bool all = n == size;
   // with everybody present a workgroup's place goes by its number, so that
-  // each XCD has a contiguous eighth of the tiles; else by its arrival
-  const int rank = all ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(s_rank);
+  // each XCD has a contiguous eighth of the tiles of a system that is alone;
+  // else by its arrival
+  const int rank = all ? seat : __builtin_amdgcn_readfirstlane(s_rank);
   if (rank < n) {
     me.rank = rank;
     me.n = n;
-    me.inx = me.nx = 0;
-    if (all) {
-      const int l = threadIdx.x & 63;
-      const int c = l < MAX_XCD ? __hip_atomic_load(&w[64 * (RUN_XCNT + l)], __ATOMIC_RELAXED, AG)
-                                : 0;
-      me.nx = __popcll(__ballot(c > 0));
-      me.inx = __builtin_amdgcn_readlane(c, me.xcd);
-    }
     const int nt = S0.ntiles, per = (nt + 7) >> 3;
-    const int first = all ? (rank & 7) * per + (rank >> 3) : rank;
-    // (all present: grid = 8 per, one tile each and none for some)
-    const int tend = all ? min(nt, ((rank & 7) + 1) * per) : nt, tstep = all ? nt : n;
+    // one: a tile each (and none for some workgroups of a system alone, whose
+    // `size` is 8 per)
+    const bool one = all && nt <= n, slab = solo && all;
+    const int first = slab ? (rank & 7) * per + (rank >> 3) : rank;
+    const int tend = slab ? min(nt, ((rank & 7) + 1) * per) : nt,
+              tstep = one ? nt : slab ? n >> 3 : n;
     // shares of a cell tile: as many units as participants where that leaves a
     // share an atom or so per thread
     const int nsp = max(1, min(8, n / S0.nctiles)), nunits = S0.nctiles * nsp;
@@ -2654,8 +2638,8 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
     bool binned = cell_only || k == bins_step;
     int dirty = 7;  // cell-layer sets to be cleared (as far as is known)
     if (clean && !idle) {
-      for (int t = first; t < tend; t += tstep) kick_tile<true>(slot(T, var), C, t, done, binned);
-      run_barrier(me, binned, S0, C, -1, out);
+      for (int t = first; t < tend; t += tstep) kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned);
+      run_barrier(me, false, S0, C, -1, out);
       err = __builtin_amdgcn_readfirstlane(out.err);
     }
     // the decisions of k_sort for step k
@@ -2702,10 +2686,10 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
       return c;
     };
     // the end of step k, with its barrier
-    auto next = [&](bool full) {
+    auto next = [&] {
       if (first == 0 && threadIdx.x < VSPREAD)
         st<true>(&gp(S0.vring)[(mod3(k + 1) * VSPREAD + threadIdx.x) * 16], 0ull);
-      run_barrier(me, full, S0, C, (int)mod3(k), out);
+      run_barrier(me, false, S0, C, (int)mod3(k), out);
       err = __builtin_amdgcn_readfirstlane(out.err);
       D2 = d1;
       V2 = V1;
@@ -2722,38 +2706,38 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
         Own<R> own;
         bool held = false;
         do {
-          SlotC &S = slot(T, var);
+          SlotC &S = slot(T, 2 * r + var);
           record();
           const bool clear = to_clear();
           for (int t = first; t < tend; t += tstep) {
             if (!held) own_load<R, MIX>(S, lds, t, k, own);
             own_step<R, ACC, MIX>(S, C, lds, t, k, k == target, clear, unord, (int)(k - done - 1),
                                   own);
-            if (!all) own_store(S, t, k + 1, own);
+            if (!one) own_store(S, t, k + 1, own);
           }
-          held = all;
-          next(false);
+          held = one;
+          next();
           if (k > end || err != 0) break;
           decide();
         } while (!rebuild);
-        if (all && first < tend) own_store(slot(T, var), first, k, own);
+        if (one && first < tend) own_store(slot(T, 2 * r + var), first, k, own);
         if (k > end || err != 0) break;
       }
       scalars();
       const int set = (int)mod3(k);
       if (!binned) {
-        SlotC &S = slot(T, var);
+        SlotC &S = slot(T, 2 * r + var);
         const int pb = (int)(k & 1);
         for (int t = first; t < tend; t += tstep) {
           const int i = t * TILE + tid_here();
           if (i < S.n)
-            bin_atom(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
+            bin_atom<true>(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
                      ld<true>(&gp((const double *)S.P[pb][1])[i]),
                      ld<true>(&gp((const double *)S.P[pb][2])[i]), k);
         }
         // (counted where binning ahead would have missed it)
         if (lead && !uniform(bins_rule(S0, force_step, k, D2, V2))) C.late_bins += 1;
-        run_barrier(me, true, S0, C, -1, out);
+        run_barrier(me, false, S0, C, -1, out);
         err = __builtin_amdgcn_readfirstlane(out.err);
         if (err != 0) break;
       }
@@ -2761,8 +2745,8 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
       SortRun sr;
       for (int u = rank; u < nunits; u += n) {
         const int t = u / nsp;
-        sort_unit(slot(T, var), slot(T, var ^ 1), C, k, MODE_STEP, reo, t, u - t * nsp, nsp, 0,
-                  sr, slds);
+        sort_unit<true>(slot(T, 2 * r + var), slot(T, 2 * r + (var ^ 1)), C, k, MODE_STEP, reo,
+                  S0.ctile_off + t, u - t * nsp, nsp, r, sr, slds);
       }
       run_barrier(me, true, S0, C, -1, out);
       if (reo) var ^= 1;
@@ -2773,10 +2757,10 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
       record();
       const bool unord = ord || S0.noreo, clear = to_clear(), bin1 = cell_only && k != target;
       for (int t = first; t < tend; t += tstep)
-        step_tile<R, ACC, MIX, true>(slot(T, var), C, lds, t, k, MODE_STEP, true, !cell_only,
+        step_tile<R, ACC, MIX, true>(slot(T, 2 * r + var), C, lds, t, k, MODE_STEP, true, !cell_only,
                                      k == target, bin1, clear,
                                      [&] { return unord; }, (int)(k - done - 1), nullptr, 0);
-      next(bin1);
+      next();
     }
     if (lead && commit && !idle) {
       const int64_t es = (int64_t)__hip_atomic_load((unsigned long long *)&C.err_step,
@@ -2787,9 +2771,48 @@ __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, 
   }
   // the last to leave clears the words for the next launch
   if (threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(&w[64 * RUN_EXIT], 1, __ATOMIC_RELAXED, AG) == (int)gridDim.x - 1)
+      __hip_atomic_fetch_add(&w[64 * RUN_EXIT], 1, __ATOMIC_RELAXED, AG) == size - 1)
     for (int q = 0; q < RUN_LINES; ++q)
       __hip_atomic_store(&w[64 * q], 0, __ATOMIC_RELAXED, AG);
+}
+
+// A system alone: one workgroup per tile.  A batch: the workgroups take the
+// seats of its replicas (seats of them in all, SlotDev::run_n each) in order;
+// one whose replica is through takes the next, so every replica goes through
+// its steps at its own pace, and none waits for another's rebuild.  Seats are
+// handed out in order and a replica's are never more than the launch has
+// workgroups, so the first replica that is not through always gets all of
+// its workgroups, or goes on with those that have come when it has waited
+// long enough.
+template <typename R, bool ACC, bool MIX>
+__global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, long long target,
+                                                         int commit, int seats) {
+  constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
+  __shared__ StepLds<MIX> lds;
+  const bool solo = seats == 0;  // a system alone: its workgroups are its seats
+  int &s_seat = ((int *)lds.sv)[2];
+  for (bool more = true; more; more = !solo) {
+    int q = blockIdx.x, r = 0;
+    if (!solo) {
+      __syncthreads();
+      if (threadIdx.x == 0)
+        s_seat = __hip_atomic_fetch_add(&T.run[0], 1, __ATOMIC_RELAXED, AG);
+      __syncthreads();
+      q = __builtin_amdgcn_readfirstlane(s_seat);
+      if (q >= seats) break;
+      r = cview(T.run_rep)[q];
+    }
+    SlotC &S0 = slot(T, 2 * r);
+    if (S0.fp64 != (sizeof(R) == 8)) continue;
+    run_replica<R, ACC, MIX>(T, lds, r, solo ? q : q - S0.run_off, solo ? (int)gridDim.x : S0.run_n,
+                             solo, steps, target, commit);
+  }
+  if (solo) return;
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(&T.run[64], 1, __ATOMIC_RELAXED, AG) == (int)gridDim.x - 1) {
+    __hip_atomic_store(&T.run[0], 0, __ATOMIC_RELAXED, AG);
+    __hip_atomic_store(&T.run[64], 0, __ATOMIC_RELAXED, AG);
+  }
 }
 
 // End of a graph replay of K steps, before k_replay_end: for every traced
@@ -2977,7 +3000,7 @@ __global__ __launch_bounds__(TILE) void k_insert(Tables T, int wrap_store, int o
     const int64_t k = cur_state(C);
     const int pb = (int)(k & 1);
     const double x = S.P[pb][0][i], y = S.P[pb][1][i], z = S.P[pb][2][i];
-    bin_atom(S, C, (int)mod3(k), i, x, y, z, k);  // checks the unwrapped coordinates
+    bin_atom<false>(S, C, (int)mod3(k), i, x, y, z, k);  // checks the unwrapped coordinates
     if (wrap_store && isfinite(x) && isfinite(y) && isfinite(z)) {
       S.P[pb][0][i] = wrap1(x, S.L, S.halfL);
       S.P[pb][1][i] = wrap1(y, S.L, S.halfL);
@@ -3140,10 +3163,10 @@ int run_capacity(int precision, bool accum, bool mix, int cus) {
   return per * cus;
 }
 hipError_t launch_run(const Tables &T, int grid, int steps, long long target, bool commit,
-                      int precision, bool accum, bool mix, hipStream_t s) {
+                      int seats, int precision, bool accum, bool mix, hipStream_t s) {
   int c = commit ? 1 : 0;
   Tables t = T;
-  void *args[] = {&t, &steps, &target, &c};
+  void *args[] = {&t, &steps, &target, &c, &seats};
   return hipLaunchKernel(run_kernel(precision, accum, mix), dim3(grid), dim3(TILE), args, 0, s);
 }
 void launch_trace(const Tables &T, int K, hipStream_t s) {

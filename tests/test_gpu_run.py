@@ -147,3 +147,27 @@ def test_two_systems_at_once():
         s.close()
     for k in range(2):
         _same(ref[k], got[k])
+
+
+def test_batch_run_equals_separate_launches():
+    """A batch whose replicas are stepped by seats (more tiles than workgroups
+    resident at once, both precisions, replicas that finish in between)
+    against the same batch in separate launches."""
+    from paper_0911_5631_amd.md import Batch
+    systems = I.replica_batch(n_replicas=40, k_lo=6, k_hi=20, steps=0, seed=12)
+    out = []
+    for two in (False, True):
+        b = Batch(1 << 33, 48, 32)
+        slots = [b.admit(s.pos, s.vel, s.box, 70 + 13 * k, shell=s.shell,
+                         precision="fp64" if k % 5 == 4 else "fp32")
+                 for k, s in enumerate(systems)]
+        if two:
+            b.configure(steps_per_run=32, sort_split=1)
+        for _ in range(4):
+            b.run()
+        done = b.poll()
+        out.append(([b.get_state(s) for s in slots], [b.props(s) for s in slots], done))
+        b.close()
+    for (p, v, n), (q, w, m) in zip(out[0][0], out[1][0]):
+        assert n == m and np.array_equal(p, q) and np.array_equal(v, w)
+    assert out[0][1] == out[1][1] and out[0][2] == out[1][2]
