@@ -50,6 +50,8 @@ constexpr int SORT_GRID = 512;     // sort workgroups of a single system (fewer,
                                    // workgroups: idle launches cost less)
 constexpr int OVF_CAP = 4096;      // per-set overflow list of cell-layer rows
 constexpr int VSPREAD = 32;        // slots of each max-speed ring entry (one per 128-byte line)
+constexpr int PK_GROUP = 8;        // packed positions tested at a time (32 a multiple of it):
+                                   // most rows hold 8 or fewer, so one round of loads
 constexpr int MAXSP = 4;           // species of a mixture
 constexpr int MAX_REPLAY = 64;     // steps of the longest replay graph
 constexpr int TRACE_RING = 65536;  // steps held by a replica's property trace

@@ -462,10 +462,11 @@ void describe(Replica *r) {
   d.noreo = g.noreo ? 1 : 0;
   d.nr = g.nr;
   d.nowin = g.nowin ? 1 : 0;
-  // packed positions: a group of candidates may read three past the last atom
+  // packed positions: a group of candidates may read past the last atom
   d.pk_scale = 65536.0 / g.L;
   const double pk_rn = g.rn * d.pk_scale + std::sqrt(3.0) + 1e-3;
-  d.pk_lim = (size_t)g.ncell * g.hcap * 4 >= (np + 4) * 8 ? (uint32_t)(pk_rn * pk_rn) + 1u : 0u;
+  d.pk_lim = (size_t)g.ncell * g.hcap * 4 >= (np + PK_GROUP) * 8
+                 ? (uint32_t)(pk_rn * pk_rn) + 1u : 0u;
   d.W = (int32_t *)r->wmat;
   d.L = g.L;
   d.halfL = 0.5 * g.L;

@@ -196,7 +196,13 @@ __device__ __forceinline__ F2 wave_sum_f2(F2 v) {
   return v;
 }
 
-__device__ __forceinline__ int64_t mod3(int64_t k) { return ((k % 3) + 3) % 3; }
+// k mod 3 for k >= -3, from its 32-bit halves (2^32 = 1 mod 3): a step's state
+// is picked by it some ten times, and a 64-bit remainder is ~50 instructions.
+__device__ __forceinline__ int64_t mod3(int64_t k) {
+  const uint64_t u = (uint64_t)(k + 3);
+  const uint32_t s = (uint32_t)u % 3u + (uint32_t)(u >> 32) % 3u;
+  return s >= 3u ? s - 3u : s;
+}
 
 // Periodic wrap into [-L/2, L/2) (exact: Sterbenz) -- idempotent.
 __device__ __forceinline__ double wrap1(double x, double L, double halfL) {
@@ -1490,7 +1496,9 @@ __device__ __forceinline__ int traverse_sorted(SlotC &S, int i, int ci, gcdouble
 // exact test runs for the ~12 per lane that pass, together with the pair
 // arithmetic, over the finished list.  Evaluation with a build, N = 256 000:
 // 63.0 -> 54.5 us, VALU instructions per wave 6 143 -> 4 325; the FP64 cell
-// method at N = 2 048 41.5 -> 35.0 us per step.
+// method at N = 2 048 41.5 -> 35.0 us per step.  Eight loads at a time instead
+// of four (and the shorter mod3): 200 steps of 864 atoms 2 334 -> 2 250 us,
+// 1 000 of 4e6 345.7 -> 340.9 ms, 200 of 110 592 LJ atoms 15.14 -> 14.95 ms.
 // EDGE: some lane of the wave is at an x-edge of the box; the other waves skip
 // the choice between the two ranges.
 template <bool EDGE, class Emit>
@@ -1569,21 +1577,21 @@ __device__ __forceinline__ void near_rows(SlotC &S, int i, int ci, const Window 
       }
       for (int c0 = 0; __ballot(c0 < tot) != 0; c0 += 32) {
         // one bit per candidate c0 .. c0+31, the first in the highest (a
-        // group of four may read up to three past its range: the array has
-        // the room, and their bits are dropped)
+        // group may read past its range: the array has the room, and the
+        // extra bits are dropped)
         auto test = [&](int lo, int k, int end) {
           uint32_t acc = 0;
           const int cnt = end - k;
           uint32_t off = 8u * (uint32_t)(lo + k);
-          for (int g = 0; g < cnt; g += 4, off += 32) {
-            pk_t c[4];
+          for (int g = 0; g < cnt; g += PK_GROUP, off += 8 * PK_GROUP) {
+            pk_t c[PK_GROUP];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) c[u] = *(gcpk)(PK + off + 8 * u);
+            for (int u = 0; u < PK_GROUP; ++u) c[u] = *(gcpk)(PK + off + 8 * u);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < PK_GROUP; ++u)
               acc = (acc << 1) | (pk_dist2(me, c[u]) <= lim ? 1u : 0u);
           }
-          return cnt > 0 ? acc >> (-cnt & 3) : 0u;
+          return cnt > 0 ? acc >> (-cnt & (PK_GROUP - 1)) : 0u;
         };
         const int end = min(tot, c0 + 32);
         uint32_t acc = test(loF, c0, EDGE ? min(lenF, end) : end);
