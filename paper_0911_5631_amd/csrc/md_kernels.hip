@@ -916,9 +916,15 @@ __device__ __forceinline__ double recip(double s) { return 1.0 / s; }
 // Pair force and energy of Eq. (1) with the soft-sphere shift: for r^2 = s,
 // f = 48 r^-8 (r^-6 - 1/2) (force on i is f d), u = 4 r^-6 (r^-6 - 1) + shift.
 // FP32 uses the refined hardware reciprocal above.
-// The energy and virial terms are summed only when ENERGY is set (a
+// The energy and virial terms are summed only when `energy` is set (a
 // wave-uniform flag: the steps whose per-atom sums somebody reads); the
-// force arithmetic is the same either way.
+// force arithmetic is the same either way.  The list loops pass a constant: with a
+// run-time flag the compiler works the terms out for every pair of every step
+// and selects (9 of the 37 VALU instructions a list entry costs, VALU issue
+// being half of a list step), and a branch over them at every pair costs as
+// much as it saves.  200 steps of 864 atoms: selects 2 250 us, a branch a pair
+// 2 323, a constant 2 209; 1 000 of 4e6: 340.9, 340.3, 337.1 ms; 200 of 32 000
+// in FP64: 2 975, 3 056, 2 902 us.
 template <typename R>
 __device__ __forceinline__ void pair_accum(Acc<R> &a, double dx, double dy, double dz, double s,
                                            R ushift, bool energy) {
@@ -2146,29 +2152,41 @@ __device__ __forceinline__ void step_tile(SlotC &S, CtlDev &C, StepLds<MIX> &lds
       if (m <= S.mcap) {
         const double rc2 = S.rc2;
         const R ushift = (R)S.ushift;
-        const bool energy = mode != MODE_STEP || last || ACC;
         // entries in order, four at a time, for as long as any lane of the wave
         // has some left: a lane past its length takes the group with no effect,
         // so the wave runs max(m)/4 groups whatever the spread of m
-        auto group = [&](auto pre, int q0, uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3) {
-          list_group<R, MIX, COH, decltype(pre)::value, NP>(a, q0, m, {e0, e1, e2, e3}, X, Y, Z, sx,
-                                                            sy, sz, xi, yi, zi, L, rc2, ushift,
-                                                            energy, tab, spi, SP, ssp, gx, gy, gz,
-                                                            gs);
+        auto group = [&](auto pre, auto en, int q0, uint32_t e0, uint32_t e1, uint32_t e2,
+                         uint32_t e3) {
+          list_group<R, MIX, COH, decltype(pre)::value, NP>(
+              a, q0, m, {e0, e1, e2, e3}, X, Y, Z, sx, sy, sz, xi, yi, zi, L, rc2, ushift,
+              decltype(en)::value, tab, spi, SP, ssp, gx, gy, gz, gs);
         };
+        auto rest = [&](auto en, int q) {
+          for (; __ballot(q < m) != 0; q += 4) {
+            uint32_t ew[4];
 #pragma unroll
-        for (int g = 0; g < NP / 4; ++g)
-          if (__ballot(4 * g < m) != 0)
-            group(std::true_type{}, 4 * g, e[4 * g], e[4 * g + 1], e[4 * g + 2], e[4 * g + 3]);
+            for (int u = 0; u < 4; ++u)
+              ew[u] = q + u < m ? (uint32_t)Wc[(size_t)(q + u) * np] : 0u;
+            group(std::false_type{}, en, q, ew[0], ew[1], ew[2], ew[3]);
+          }
+        };
+        // (outside a block few steps sum energies: they read their entries
+        // again, so that the loaded ones need one loop)
+        if (!ACC && (mode != MODE_STEP || last)) {
+          rest(std::true_type{}, 0);
+        } else {
+          constexpr std::bool_constant<ACC> en{};
 #pragma unroll
-        for (int g = NP / 4; g < NE / 4; ++g)
-          if (__ballot(4 * g < m) != 0)
-            group(std::false_type{}, 4 * g, e[4 * g], e[4 * g + 1], e[4 * g + 2], e[4 * g + 3]);
-        for (int q = NE; __ballot(q < m) != 0; q += 4) {
-          uint32_t ew[4];
+          for (int g = 0; g < NP / 4; ++g)
+            if (__ballot(4 * g < m) != 0)
+              group(std::true_type{}, en, 4 * g, e[4 * g], e[4 * g + 1], e[4 * g + 2],
+                    e[4 * g + 3]);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) ew[u] = q + u < m ? (uint32_t)Wc[(size_t)(q + u) * np] : 0u;
-          group(std::false_type{}, q, ew[0], ew[1], ew[2], ew[3]);
+          for (int g = NP / 4; g < NE / 4; ++g)
+            if (__ballot(4 * g < m) != 0)
+              group(std::false_type{}, en, 4 * g, e[4 * g], e[4 * g + 1], e[4 * g + 2],
+                    e[4 * g + 3]);
+          rest(en, NE);
         }
       } else {
         // the list overflowed its capacity at the last build: evaluate this
@@ -2259,20 +2277,30 @@ __device__ __forceinline__ void own_step(SlotC &S, CtlDev &C, StepLds<MIX> &lds,
     if (m <= S.mcap) {
       const auto W = gp((const int32_t *)S.W) + i;
       const size_t np = (size_t)S.npad;
-      auto group = [&](int q0, Four f) {
+      auto group = [&](auto en, int q0, Four f) {
         list_group<R, MIX, true, false, 4>(a, q0, m, f, X, Y, Z, sx, sy, sz, o.x[0], o.x[1], o.x[2],
-                                           L, rc2, ushift, energy, tab, o.sp, SP, ssp, nullptr,
-                                           nullptr, nullptr, nullptr);
+                                           L, rc2, ushift, decltype(en)::value, tab, o.sp, SP, ssp,
+                                           nullptr, nullptr, nullptr, nullptr);
       };
+      auto rest = [&](auto en, int q) {
+        for (; __ballot(q < m) != 0; q += 4) {
+          Four f;
 #pragma unroll
-      for (int g = 0; g < NR / 4; ++g)
-        if (__ballot(4 * g < m) != 0)
-          group(4 * g, {o.e[4 * g], o.e[4 * g + 1], o.e[4 * g + 2], o.e[4 * g + 3]});
-      for (int q = NR; __ballot(q < m) != 0; q += 4) {
-        Four f;
+          for (int u = 0; u < 4; ++u) f.e[u] = q + u < m ? (uint32_t)W[(size_t)(q + u) * np] : 0u;
+          group(en, q, f);
+        }
+      };
+      // (only a run's last step sums energies outside a block: its entries
+      // are read again, so that the held ones need one loop)
+      if (!ACC && last) {
+        rest(std::true_type{}, 0);
+      } else {
+        constexpr std::bool_constant<ACC> en{};
 #pragma unroll
-        for (int u = 0; u < 4; ++u) f.e[u] = q + u < m ? (uint32_t)W[(size_t)(q + u) * np] : 0u;
-        group(q, f);
+        for (int g = 0; g < NR / 4; ++g)
+          if (__ballot(4 * g < m) != 0)
+            group(en, 4 * g, {o.e[4 * g], o.e[4 * g + 1], o.e[4 * g + 2], o.e[4 * g + 3]});
+        rest(en, NR);
       }
     } else {
       // its list overflowed: over the 27 cells of its cell at the last sort
