@@ -194,7 +194,7 @@ struct Engine {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipEvent_t ev_t[2] = {nullptr, nullptr};  // timing events of the A/B launches
   void *h_scalar = nullptr;                 // pinned: scalars read back from the device
-  char *h_io = nullptr;                     // pinned: two buffers of io_half bytes that state
+  char *h_io = nullptr;                     // pinned: buffer(s) of io_half bytes that state
   size_t io_half = 0;                       // passes through (ensure_io)
   hipEvent_t ev_io[2] = {nullptr, nullptr};
   int device = 0;
@@ -783,9 +783,9 @@ void copy_host(void *dst, const void *src, size_t bytes) {
   for (int k = 0; k < used; ++k) t[k].join();
 }
 
-// The pinned buffers that state passes through, each with room for `want`
-// bytes or IO_MAX (they are kept with the engine: allocating pinned memory at
-// every call took longer than the transfer).
+// The pinned buffers that state passes through: one with room for `want` bytes,
+// or two of IO_MAX for what takes several runs (kept with the engine:
+// allocating pinned memory at every call took longer than the transfer).
 constexpr size_t IO_MAX = 16u << 20;
 md_status ensure_io(Engine *e, size_t want) {
   want = std::min(std::max(round_up(want, 4096), (size_t)65536), IO_MAX);
@@ -797,7 +797,8 @@ md_status ensure_io(Engine *e, size_t want) {
     e->io_half = 0;
     if (err != hipSuccess) return e->fail("pinned staging", err);
   }
-  const hipError_t err = hipHostMalloc((void **)&e->h_io, 2 * want, hipHostMallocDefault);
+  const size_t bytes = want < IO_MAX ? want : 2 * IO_MAX;
+  const hipError_t err = hipHostMalloc((void **)&e->h_io, bytes, hipHostMallocDefault);
   if (err != hipSuccess) {
     e->h_io = nullptr;
     return e->fail("pinned staging", err);
@@ -812,7 +813,7 @@ md_status ensure_io(Engine *e, size_t want) {
 md_status upload_state(Engine *e, Replica *r, int variant, int64_t step, const double *pos,
                        const double *vel) {
   const int64_t n = r->g.n;
-  md_status st = ensure_io(e, (size_t)n * 48);
+  md_status st = ensure_io(e, (size_t)n * 72);  // room for md_get_state's arrays too
   if (st != MD_OK) return st;
   const int64_t cap = (int64_t)(e->io_half / 48);
   hipError_t err = hipSuccess;
