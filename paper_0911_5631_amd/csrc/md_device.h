@@ -165,14 +165,18 @@ struct CtlDev {
                        // RB_REORDER into the other variant, RB_PERM in place
   int32_t ord_ring[3]; // 1 if the storage of state k is not the cell order of the last
                        // sort (it rebuilt without reordering since), slot k % 3
-  int32_t bin_ring[3]; // 1 if step k bins r(k+1) (decided by k_sort of step k), slot k % 3
+  int32_t bin_ring[3]; // 1 if step k (or the kick of state k) binned r(k+1) into its set,
+                       // slot k % 3: decided and recorded by k_sort of step k; k_run
+                       // records what it did.  A sort of step k + 1 reads it, so a
+                       // batch can change between the two from run to run
   int32_t err;         // latched ERR_* bits
   int32_t max_h;       // largest cell occupancy seen by a sort
   int32_t late_bins;   // rebuilds of k_run whose positions were not binned ahead
   // properties reduced by k_props
   double ke, pe, vir, vmax2;
   int64_t sum_m;
-  int32_t max_m, pad0;
+  int32_t max_m;
+  int32_t bin_due;     // k_due found r(done+1) to be binned by k_bin_due
   // block sums reduced by k_props from SlotDev::acc
   double acc_sum[NACC];
 };

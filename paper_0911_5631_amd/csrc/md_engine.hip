@@ -212,6 +212,7 @@ struct Engine {
   int run_cap[2][2][2] = {};    // k_run's workgroups resident at once, + 1 (0: not asked yet)
   int32_t *d_run_rep = nullptr; // a batch's seats in k_run (Tables::run_rep)
   int run_rep_cap = 0, run_seats = 0, run_most = 0;  // room, seats in use, most of one replica
+  bool ran = false;             // the last md_batch_run went through k_run
   int tile_cap = 0, ctile_cap = 0;
   CtlDev *h_ctl = nullptr;      // pinned
   SlotDev *h_slots = nullptr;   // pinned [2 * max_slots]
@@ -2161,7 +2162,13 @@ md_status md_batch_run(md_batch *b) {
       launch_replay_end(T, e->steps_per_run, e->work);
     }
     if ((st = e->check("run launches")) != MD_OK) return st;
+    e->ran = true;
     return v.leave();
+  }
+  if (e->ran) {
+    launch_bin_due(e->tables(), e->grid, e->work);
+    if ((st = e->check("bin launches")) != MD_OK) return st;
+    e->ran = false;
   }
   launch_kick(e->tables(), e->grid, e->work);
   if ((st = e->check("kick")) != MD_OK) return st;

@@ -41,6 +41,9 @@ void launch_props(const Tables &T, int only, CtlDev *ctl_out, hipStream_t s);
 void launch_adjust(const Tables &T, int grid, int only, double temperature, hipStream_t s);
 // Bin the held state into its cell-layer set (optionally wrapping in place).
 void launch_insert(const Tables &T, int grid, int wrap_store, int only, hipStream_t s);
+// Replicas that k_run left in mid-run: bin the held r(done + 1) where the
+// launches of a step would have binned it ahead.
+void launch_bin_due(const Tables &T, int grid, hipStream_t s);
 // Counting sort by cell into the other buffer variant: in a step
 // (MODE_STEP, step index s of the replay; only where the rebuild rule fires)
 // or of the held clean state (any other mode; follow with launch_flip).

@@ -406,9 +406,10 @@ __device__ __forceinline__ X pick3(X a0, X a1, X a2, int64_t e) {
 // rebuild_rule, accumulated with BIN_AHEAD times the maximum speed of step
 // k-2 (that of step k-1 is not known while step k-1 runs), would fire at
 // step k.  The sort of step k-1, which holds every input of the rule, takes
-// this decision for the step kernel of step k-1 (CtlDev::bin_ring); the sort
-// of step k evaluates the same expression from the same committed words, so
-// it knows whether the rows exist; when the rule fires
+// this decision for the step kernel of step k-1 and records it
+// (CtlDev::bin_ring); the sort of step k reads there whether the rows exist
+// (k_run, which takes the same replicas, bins only when the rule has fired, so
+// the rule itself does not tell).  When the rule fires
 // without them (the maximum speed grew by more than BIN_AHEAD in one step)
 // it latches ERR_UNBINNED and the host bins r(k) and resumes, so the
 // trajectory does not depend on the guess.  Called by whole waves.
@@ -476,6 +477,8 @@ __global__ __launch_bounds__(TILE) void k_kick(Tables T) {
     if ((C.err != 0 && C.err_step <= C.done) || !C.clean || C.done >= C.target) continue;
     const int64_t k = C.done;
     const bool bin = bins_due(slot(T, 2 * r), C, k + 1);
+    // (nobody reads this word in this launch)
+    if (t == S.tile_off && threadIdx.x == 0) C.bin_ring[mod3(k)] = bin ? 1 : 0;
     kick_tile<false>(S, C, t - S.tile_off, k, bin);
   }
 }
@@ -792,6 +795,7 @@ __global__ __launch_bounds__(TILE, 4) void k_sort(Tables T, int s, int mode, int
       const int64_t ro0 = C.reo_ring[0], ro1 = C.reo_ring[1], ro2 = C.reo_ring[2];
       const double dp0 = C.disp_ring[0], dp1 = C.disp_ring[1], dp2 = C.disp_ring[2];
       const int32_t vr0 = C.var_ring[0], vr1 = C.var_ring[1], vr2 = C.var_ring[2];
+      const int32_t bn0 = C.bin_ring[0], bn1 = C.bin_ring[1], bn2 = C.bin_ring[2];
       double vm[3];
       ring_max3(S0, vm);
       k = base + s + 1;
@@ -803,8 +807,7 @@ __global__ __launch_bounds__(TILE, 4) void k_sort(Tables T, int s, int mode, int
       d1 = 0.0;
       const double V1 = pick3(vm[0], vm[1], vm[2], e1);
       if (!S0.cell_only) rebuild = rebuild_rule(S0, force_step, k, D2, V1, &d1);
-      unbinned = rebuild && !bins_rule(S0, force_step, k, D2, pick3(vm[0], vm[1], vm[2], e2)) &&
-                 k != bins_step;
+      unbinned = rebuild && pick3(bn0, bn1, bn2, e1) == 0 && k != bins_step;
       // the step kernel's binning ahead for step k + 1 (see bins_due): the
       // rule of step k + 1 from the displacement after step k-1 (d1, which
       // this launch commits) and the maximum speed of step k-1
@@ -2605,6 +2608,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
   const auto &C0 = *cview(T.ctl + r);
   const int64_t target = to < 0 ? C0.target : (int64_t)to;
   const int64_t done = C0.done, force_step = C0.force_step, bins_step = C0.bins_step;
+  const bool ahead = C0.bin_ring[mod3(done)] != 0;
   const int64_t end = done + steps < target ? done + steps : target;
   const bool clean = C0.clean != 0, cell_only = S0.cell_only != 0;
   int64_t k = done + 1;
@@ -2616,7 +2620,8 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
   const bool idle = C0.err != 0 || done >= end;
   // (read here: a workgroup that comes after the others have gone on may find
   // other words, and takes no part)
-  asm volatile("" ::"s"(done), "s"(target), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean));
+  asm volatile("" ::"s"(done), "s"(target), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean),
+               "s"((int)ahead), "s"(bins_step));
   // roll call
   RunSeat me;
   me.w = w;
@@ -2666,12 +2671,15 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     if (lead) {
       C.target = target;
       C.base = done;
+      if (clean && !idle) C.bin_ring[mod3(done)] = cell_only ? 1 : 0;
     }
     // With a list, a sort's positions are binned when the rule has fired: here
     // that is a barrier more, where binning ahead (see bins_rule) costs a step
     // its atomics and a full barrier about one and a half times per rebuild.
-    // With the cell method every step bins the next one's.
-    bool binned = cell_only || k == bins_step;
+    // With the cell method every step bins the next one's.  (A replica of a
+    // batch that the two launches left in mid-run holds r(k) binned where
+    // bin_ring says so.)
+    bool binned = (clean ? cell_only : ahead) || k == bins_step;
     int dirty = 7;  // cell-layer sets to be cleared (as far as is known)
     if (clean && !idle) {
       for (int t = first; t < tend; t += tstep) kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned);
@@ -2706,7 +2714,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     auto record = [&] {
       if (!lead) return;
       C.rb_ring[mod3(k)] = rebuild ? (reo ? RB_REORDER : RB_PERM) : RB_NONE;
-      C.bin_ring[mod3(k)] = 0;
+      C.bin_ring[mod3(k)] = cell_only && k != target ? 1 : 0;
       C.reo_ring[mod3(k)] = reo1;
       if (!cell_only) {
         C.disp_ring[mod3(k - 1)] = d1;
@@ -3023,6 +3031,38 @@ __global__ __launch_bounds__(TILE) void k_adjust(Tables T, int only, double temp
 // ---------------------------------------------------------------------------
 // binning of the held state outside a step (creation, host-side sorts)
 // ---------------------------------------------------------------------------
+// A batch goes on from k_run in two launches a step: its replicas in mid-run
+// hold r(done + 1) unbinned, where those launches would have binned it ahead
+// if bins_due.  k_due (one wave per replica) finds the replicas to be binned
+// and records it, k_bin_due bins them; without it every one whose rule fires
+// at once would wait for the host.
+__global__ __launch_bounds__(64) void k_due(Tables T) {
+  const int r = blockIdx.x;
+  SlotC &S0 = slot(T, 2 * r);
+  if (S0.n <= 0) return;
+  CtlDev &C = T.ctl[r];
+  const int64_t k = C.done + 1;
+  const bool due = C.err == 0 && !C.clean && k <= C.target && k != C.bins_step &&
+                   C.bin_ring[mod3(C.done)] == 0 && bins_due(S0, C, k);
+  if (threadIdx.x == 0) {
+    C.bin_due = due ? 1 : 0;
+    if (due) C.bin_ring[mod3(k - 1)] = 1;
+  }
+}
+__global__ __launch_bounds__(TILE) void k_bin_due(Tables T) {
+  const int nt = T.hdr[HDR_NTILES];
+  for (int t = xcd_block(blockIdx.x, gridDim.x); t < nt; t += gridDim.x) {
+    const int r = T.tile_rep[t];
+    CtlDev &C = T.ctl[r];
+    if (slot(T, 2 * r).n <= 0 || C.bin_due == 0) continue;
+    SlotC &S = slot_held(T, r);
+    const int i = (t - S.tile_off) * TILE + threadIdx.x;
+    if (i >= S.n) continue;
+    const int64_t k = C.done + 1;
+    const int pb = (int)(k & 1);
+    bin_atom<false>(S, C, (int)mod3(k), i, S.P[pb][0][i], S.P[pb][1][i], S.P[pb][2][i], k);
+  }
+}
 __global__ __launch_bounds__(TILE) void k_insert(Tables T, int wrap_store, int only) {
   const int nt = T.hdr[HDR_NTILES];
   for (int t = xcd_block(blockIdx.x, gridDim.x); t < nt; t += gridDim.x) {
@@ -3222,6 +3262,10 @@ void launch_adjust(const Tables &T, int grid, int only, double temperature, hipS
 }
 void launch_insert(const Tables &T, int grid, int wrap_store, int only, hipStream_t s) {
   hipLaunchKernelGGL(k_insert, dim3(grid), dim3(TILE), 0, s, T, wrap_store, only);
+}
+void launch_bin_due(const Tables &T, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_due, dim3(T.nslots), dim3(64), 0, s, T);
+  hipLaunchKernelGGL(k_bin_due, dim3(grid), dim3(TILE), 0, s, T);
 }
 void launch_cells(const Tables &T, int grid, int only, int32_t *out, hipStream_t s) {
   hipLaunchKernelGGL(k_cells, dim3(grid), dim3(TILE), 0, s, T, only, out);
