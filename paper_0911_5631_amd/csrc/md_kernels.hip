@@ -243,9 +243,9 @@ __device__ __forceinline__ void latch_error(CtlDev &C, int bits, int64_t step) {
 
 // A new position of step `step`: latch an error for a non-finite coordinate
 // or one outside [-3L/2, 3L/2) (the wrap at the next rebuild could not bring
-// it back); returns false for a non-finite one.
-__device__ __forceinline__ bool check_atom(SlotC &S, CtlDev &C, double x, double y, double z,
-                                           int64_t step) {
+// it back); returns its bit, or 0.
+__device__ __forceinline__ int check_atom(SlotC &S, CtlDev &C, double x, double y, double z,
+                                          int64_t step) {
   int bad = 0;
   if (!(isfinite(x) && isfinite(y) && isfinite(z))) {
     bad = ERR_NONFINITE;
@@ -253,19 +253,21 @@ __device__ __forceinline__ bool check_atom(SlotC &S, CtlDev &C, double x, double
     bad = ERR_ESCAPED;
   }
   if (bad) latch_error(C, bad, step);
-  return bad != ERR_NONFINITE;
+  return bad;
 }
 
 // Cell and layer assignment of one atom (Secs. 3.2, 3.4): the atom's cell
 // from its wrapped coordinates, a layer slot from the cell's occupancy
 // counter (atomic), the row entry, or the set's overflow list beyond hcap.
 // The sort of a rebuild step reads the rows; the cell each atom lands in
-// there is written by the sort itself.
+// there is written by the sort itself.  Returns the error latched for this
+// atom, or 0.
 template <bool COH>
-__device__ __forceinline__ void bin_atom(SlotC &S, CtlDev &C, int set, int i, double x, double y,
-                         double z, int64_t step) {
+__device__ __forceinline__ int bin_atom(SlotC &S, CtlDev &C, int set, int i, double x, double y,
+                                        double z, int64_t step) {
   // Called by a prefix of the lanes of a wave (the active atoms of a tile).
-  if (!check_atom(S, C, x, y, z, step)) x = y = z = 0.0;
+  int bad = check_atom(S, C, x, y, z, step);
+  if (bad == ERR_NONFINITE) x = y = z = 0.0;
   const int c = cell_of(S, wrap1(x, S.L, S.halfL), wrap1(y, S.L, S.halfL), wrap1(z, S.L, S.halfL));
   // Consecutive lanes with the same cell take their layer slots with one
   // atomic: atoms are stored in cell order, so most of a cell's atoms are
@@ -305,8 +307,10 @@ __device__ __forceinline__ void bin_atom(SlotC &S, CtlDev &C, int set, int i, do
       st<COH>(&gp(S.ovf[set])[2 * o + 1], i);
     } else {
       latch_error(C, ERR_CELL, step);
+      bad |= ERR_CELL;
     }
   }
+  return bad;
 }
 
 #define MD_CX(p, q)                             \
@@ -444,11 +448,12 @@ __device__ __forceinline__ bool rebuild_rule(const SlotC &S, int64_t force_step,
 // ---------------------------------------------------------------------------
 // (a): first half kick and drift of a clean replica, and binning of r(k+1)
 // ---------------------------------------------------------------------------
-// One tile of a clean replica at state k; bin: r(k+1) into its set.
+// One tile of a clean replica at state k; bin: r(k+1) into its set.  Returns
+// the error latched for the thread's atom, or 0.
 template <bool COH>
-__device__ __forceinline__ void kick_tile(SlotC &S, CtlDev &C, int lt, int64_t k, bool bin) {
+__device__ __forceinline__ int kick_tile(SlotC &S, CtlDev &C, int lt, int64_t k, bool bin) {
   const int i = lt * TILE + threadIdx.x;
-  if (i >= S.n) return;
+  if (i >= S.n) return 0;
   const int pb = (int)(k & 1), vb = (int)((k + 1) & 1);
   double f[3];
   for (int a = 0; a < 3; ++a)
@@ -461,10 +466,8 @@ __device__ __forceinline__ void kick_tile(SlotC &S, CtlDev &C, int lt, int64_t k
     xn[a] = gp(S.P[pb][a])[i] + S.dt * v;
     st<COH>(&gp(S.P[pb ^ 1][a])[i], xn[a]);
   }
-  if (bin)
-    bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
-  else
-    check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+  return bin ? bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1)
+             : check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
 }
 __global__ __launch_bounds__(TILE) void k_kick(Tables T) {
   const int nt = T.hdr[HDR_NTILES];
@@ -1784,6 +1787,7 @@ struct StepLds {
   int8_t ssp[MIX ? WCAP + 4 : 1];
   unsigned long long sv[4];
   double sh[4][8];
+  int bad;  // k_run: this workgroup has latched an error
 };
 // The end of a tile's step: (d), (e) and the next (a) -- x and v become those
 // of the next step -- the binning of r(k+1) where bin_next, the clearing of
@@ -1820,10 +1824,10 @@ __device__ __forceinline__ void finish_tile(SlotC &S, CtlDev &C, Lds &lds, int l
           else
             __builtin_nontemporal_store(xn[q], &gp(S.P[pb ^ 1][q])[i]);
         }
-        if (bin_next)
-          bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1);
-        else
-          check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+        const int bad =
+            bin_next ? bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1)
+                     : check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
+        if (COH && bad) lds.bad = 1;
       }
       if (put_v)
         for (int q = 0; q < 3; ++q) {
@@ -2504,7 +2508,8 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 // The others find the launch committed without them and leave.  Everybody
 // who takes part is running and stays so, so every barrier completes, and
 // with fewer participants than tiles each steps several.  (The spin bound of
-// the barriers is a backstop: it latches ERR_STALL.)
+// the barriers is a backstop: it latches ERR_STALL, and none of the launch's
+// steps is counted.)
 //
 // What is shared: everything that another workgroup may read in the same
 // launch is stored device-scope (st) and read so (ld), past the caches that
@@ -2530,17 +2535,24 @@ struct RunSeat {
   int32_t *w;
   int rank, n, epoch;
 };
-// The maximum speed of a ring entry and the error word as of a barrier.
+// The maximum speed of a ring entry as of a barrier, and whether the run stops
+// there.
 struct RunOut {
   unsigned long long vbits;
-  int err;
+  int stop;
 };
-__device__ __forceinline__ bool run_wait(int32_t *f, int v) {
+// A counter of arrivals also counts, from this bit on, those that bring an
+// error (a launch's arrivals at one counter stay below it: 32 workgroups of a
+// group times some 800 barriers); the epoch word carries RUN_STOP.
+constexpr int RUN_BAD = 1 << 20, RUN_STOP = 1 << 30;
+// The epoch word once it has reached epoch v, or -1.
+__device__ __forceinline__ int run_wait(int32_t *f, int v) {
   for (int it = 0; it < RUN_SPINS; ++it) {
-    if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= v) return true;
+    const int e = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((e & (RUN_STOP - 1)) >= v) return e;
     __builtin_amdgcn_s_sleep(1);
   }
-  return false;
+  return -1;
 }
 
 // The grid barrier.  Arrivals are counted in 32 groups, then over the groups:
@@ -2548,37 +2560,50 @@ __device__ __forceinline__ bool run_wait(int32_t *f, int v) {
 // drop: plain loads after it see what was stored (device-scope) before it:
 // the caches of the CU and of its XCD are invalidated, by one wave for its
 // workgroup.
-// The maximum speed of ring entry e (e < 0: none) and the error word are left
-// in `out`.
-__device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, SlotC &S0, CtlDev &C, int e,
-                                            RunOut &out) {
+// ring: the maximum speed of that ring entry (< 0: none) is left in `out`,
+// read by one wave.
+// Whether the run stops is one decision for all: it goes with the epoch, from
+// what every workgroup brought (`bad`).  (The error word itself may already
+// hold an error of the next phase, which a workgroup that was quicker is in:
+// one that acted on it would leave the others waiting.)  A workgroup whose
+// barrier gives up stops, and brings that to the next one it comes to.
+__device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, int ring, SlotC &S0, CtlDev &C,
+                                            int &bad, RunOut &out) {
   constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
   int32_t *w = p.w;
   __builtin_amdgcn_s_waitcnt(0);  // this wave's device-scope stores have arrived
   __syncthreads();
   ++p.epoch;
   if (threadIdx.x < 64) {
-    bool ok = true;
+    int e = 0;
     if (threadIdx.x == 0) {
       const int g = p.rank & (RUN_GROUPS - 1), in = (p.n - g + RUN_GROUPS - 1) / RUN_GROUPS;
       const int ng = p.n < RUN_GROUPS ? p.n : RUN_GROUPS;
-      if (__hip_atomic_fetch_add(&w[64 * g], 1, __ATOMIC_RELAXED, AG) == p.epoch * in - 1 &&
-          __hip_atomic_fetch_add(&w[64 * RUN_ROOT], 1, __ATOMIC_RELAXED, AG) == p.epoch * ng - 1)
-        __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch, __ATOMIC_RELAXED, AG);
-      ok = run_wait(&w[64 * RUN_EPOCH], p.epoch);
+      const int mine = bad ? RUN_BAD + 1 : 1;
+      const int got = __hip_atomic_fetch_add(&w[64 * g], mine, __ATOMIC_RELAXED, AG) + mine;
+      if ((got & (RUN_BAD - 1)) == p.epoch * in) {
+        const int ours = got >= RUN_BAD ? RUN_BAD + 1 : 1;
+        const int all = __hip_atomic_fetch_add(&w[64 * RUN_ROOT], ours, __ATOMIC_RELAXED, AG) + ours;
+        if ((all & (RUN_BAD - 1)) == p.epoch * ng)
+          __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch | (all >= RUN_BAD ? RUN_STOP : 0),
+                             __ATOMIC_RELAXED, AG);
+      }
+      e = run_wait(&w[64 * RUN_EPOCH], p.epoch);
+      if (e < 0) {
+        latch_error(C, ERR_STALL, C.done + 1);
+        bad = 1;
+      }
     }
-    if (!ok) atomicOr(&C.err, ERR_STALL);
     __builtin_amdgcn_s_waitcnt(0);
     // (the loads below come back after the invalidation)
     if (drop) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     unsigned long long v = 0;
-    if (e >= 0 && threadIdx.x < VSPREAD)
-      v = __hip_atomic_load(&S0.vring[(e * VSPREAD + threadIdx.x) * 16], __ATOMIC_RELAXED, AG);
-    const int err = __hip_atomic_load(&C.err, __ATOMIC_RELAXED, AG);
+    if (ring >= 0 && threadIdx.x < VSPREAD)
+      v = __hip_atomic_load(&S0.vring[(ring * VSPREAD + threadIdx.x) * 16], __ATOMIC_RELAXED, AG);
     v = wave_max_u64(v);
     if (threadIdx.x == 0) {
       out.vbits = v;
-      out.err = err;
+      out.stop = e < 0 || (e & RUN_STOP) != 0 ? 1 : 0;
     }
   }
   __syncthreads();
@@ -2618,10 +2643,11 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
   int64_t reo1 = C0.reo_ring[mod3(k - 1)];
   bool ord = C0.ord_ring[mod3(k - 1)] != 0;
   const bool idle = C0.err != 0 || done >= end;
-  // (read here: a workgroup that comes after the others have gone on may find
-  // other words, and takes no part)
+  // (read here, every word: a workgroup that comes after the others have gone
+  // on may find other words, and takes no part)
   asm volatile("" ::"s"(done), "s"(target), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean),
-               "s"((int)ahead), "s"(bins_step));
+               "s"((int)ahead), "s"(bins_step), "s"((int)idle), "s"(force_step),
+               "s"(__double_as_longlong(D2)));
   // roll call
   RunSeat me;
   me.w = w;
@@ -2645,6 +2671,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     }
     s_rank = rank;
     s_n = n;
+    lds.bad = 0;
   }
   __syncthreads();
   const int n = __builtin_amdgcn_readfirstlane(s_n);
@@ -2667,7 +2694,11 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     // share an atom or so per thread
     const int nsp = max(1, min(8, n / S0.nctiles)), nunits = S0.nctiles * nsp;
     const bool lead = rank == 0 && threadIdx.x == 0;
-    int err = idle ? 1 : 0;  // nothing to do: the loop below is not entered
+    int stop = idle ? 1 : 0;  // nothing to do: the loop below is not entered
+    auto barrier = [&](bool drop, bool ring) {
+      run_barrier(me, drop, ring ? (int)mod3(k) : -1, S0, C, lds.bad, out);
+      stop = __builtin_amdgcn_readfirstlane(out.stop);
+    };
     if (lead) {
       C.target = target;
       C.base = done;
@@ -2682,9 +2713,9 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     bool binned = (clean ? cell_only : ahead) || k == bins_step;
     int dirty = 7;  // cell-layer sets to be cleared (as far as is known)
     if (clean && !idle) {
-      for (int t = first; t < tend; t += tstep) kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned);
-      run_barrier(me, false, S0, C, -1, out);
-      err = __builtin_amdgcn_readfirstlane(out.err);
+      for (int t = first; t < tend; t += tstep)
+        if (kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned)) lds.bad = 1;
+      barrier(false, false);
     }
     // the decisions of k_sort for step k
     double d1 = 0.0;
@@ -2733,15 +2764,14 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     auto next = [&] {
       if (first == 0 && threadIdx.x < VSPREAD)
         st<true>(&gp(S0.vring)[(mod3(k + 1) * VSPREAD + threadIdx.x) * 16], 0ull);
-      run_barrier(me, false, S0, C, (int)mod3(k), out);
-      err = __builtin_amdgcn_readfirstlane(out.err);
+      barrier(false, true);
       D2 = d1;
       V2 = V1;
       V1 = uniform(__longlong_as_double((long long)out.vbits));
       binned = cell_only;
       ++k;
     };
-    while (k <= end && err == 0) {
+    while (k <= end && stop == 0) {
       decide();
       if (!rebuild) {
         // the list steps up to the next rebuild; with one tile per workgroup it
@@ -2761,11 +2791,11 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
           }
           held = one;
           next();
-          if (k > end || err != 0) break;
+          if (k > end || stop != 0) break;
           decide();
         } while (!rebuild);
         if (one && first < tend) own_store(slot(T, 2 * r + var), first, k, own);
-        if (k > end || err != 0) break;
+        if (k > end || stop != 0) break;
       }
       scalars();
       const int set = (int)mod3(k);
@@ -2774,16 +2804,15 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
         const int pb = (int)(k & 1);
         for (int t = first; t < tend; t += tstep) {
           const int i = t * TILE + tid_here();
-          if (i < S.n)
-            bin_atom<true>(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
-                     ld<true>(&gp((const double *)S.P[pb][1])[i]),
-                     ld<true>(&gp((const double *)S.P[pb][2])[i]), k);
+          if (i < S.n && bin_atom<true>(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
+                                        ld<true>(&gp((const double *)S.P[pb][1])[i]),
+                                        ld<true>(&gp((const double *)S.P[pb][2])[i]), k))
+            lds.bad = 1;
         }
         // (counted where binning ahead would have missed it)
         if (lead && !uniform(bins_rule(S0, force_step, k, D2, V2))) C.late_bins += 1;
-        run_barrier(me, false, S0, C, -1, out);
-        err = __builtin_amdgcn_readfirstlane(out.err);
-        if (err != 0) break;
+        barrier(false, false);
+        if (stop != 0) break;
       }
       scalars();
       SortRun sr;
@@ -2792,7 +2821,9 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
         sort_unit<true>(slot(T, 2 * r + var), slot(T, 2 * r + (var ^ 1)), C, k, MODE_STEP, reo,
                   S0.ctile_off + t, u - t * nsp, nsp, r, sr, slds);
       }
-      run_barrier(me, true, S0, C, -1, out);
+      barrier(true, false);
+      // (an exit of its own here costs the loop's state a score of registers)
+      const int tdone = stop != 0 ? 0 : tend;
       if (reo) var ^= 1;
       ord = !reo;
       if (reo) reo1 = k;
@@ -2800,7 +2831,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
       scalars();
       record();
       const bool unord = ord || S0.noreo, clear = to_clear(), bin1 = cell_only && k != target;
-      for (int t = first; t < tend; t += tstep)
+      for (int t = first; t < tdone; t += tstep)
         step_tile<R, ACC, MIX, true>(slot(T, 2 * r + var), C, lds, t, k, MODE_STEP, true, !cell_only,
                                      k == target, bin1, clear,
                                      [&] { return unord; }, (int)(k - done - 1), nullptr, 0);
