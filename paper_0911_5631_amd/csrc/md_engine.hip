@@ -515,7 +515,6 @@ void describe(Replica *r) {
   }
 }
 
-// Rebuild the tile tables and upload the descriptors of every slot (sync).
 // Tile order of the step kernel in use: the one asked for, else passes for
 // a batch (its systems rebuild at different steps, so the cost of the tiles
 // is uneven and is best spread over every XCD) and XCD slabs for a single
@@ -525,6 +524,24 @@ int tile_order(const Engine *e) {
   return e->batch ? MD_ORDER_PASSES : MD_ORDER_SLABS;
 }
 
+// Room for `need` ints in a device table (the stream is idle).  The old table
+// stays until there is a larger one, so an engine whose allocator refuses goes
+// on with the systems it has.
+bool grow_table(Engine *e, int32_t **table, int *cap, int need) {
+  if (need <= *cap) return true;
+  const int room = std::max(need, 2 * *cap);
+  int32_t *t = (int32_t *)e->dmalloc((size_t)room * 4);
+  if (!t) return false;
+  // the captured graphs hold the table pointers in their kernel arguments
+  for (auto &kv : e->graphs) (void)hipGraphExecDestroy(kv.second);
+  e->graphs.clear();
+  e->dfree(*table);
+  *table = t;
+  *cap = room;
+  return true;
+}
+
+// Rebuild the tile tables and upload the descriptors of every slot (sync).
 md_status upload_tables(Engine *e) {
   hipError_t err = hipStreamSynchronize(e->work);
   if (err != hipSuccess) return e->fail("upload tables", err);
@@ -541,19 +558,9 @@ md_status upload_tables(Engine *e) {
     nt += r->g.ntiles;
     nct += r->g.nctiles;
   }
-  if (nt > e->tile_cap || nct > e->ctile_cap) {
-    // the captured graphs hold the table pointers in their kernel arguments:
-    // drop them before the tables move (the stream is idle here)
-    for (auto &kv : e->graphs) (void)hipGraphExecDestroy(kv.second);
-    e->graphs.clear();
-    e->dfree(e->d_tile_rep);
-    e->dfree(e->d_ctile_rep);
-    e->tile_cap = std::max(nt, 2 * e->tile_cap);
-    e->ctile_cap = std::max(nct, 2 * e->ctile_cap);
-    e->d_tile_rep = (int32_t *)e->dmalloc((size_t)e->tile_cap * 4);
-    e->d_ctile_rep = (int32_t *)e->dmalloc((size_t)e->ctile_cap * 4);
-    if (!e->d_tile_rep || !e->d_ctile_rep) return MD_ERR_OOM;
-  }
+  if (!grow_table(e, &e->d_tile_rep, &e->tile_cap, nt) ||
+      !grow_table(e, &e->d_ctile_rep, &e->ctile_cap, nct))
+    return MD_ERR_OOM;
   // a batch's seats in k_run: one per tile, the largest replicas first (each
   // takes about as long as any other, and the small ones fill what is left)
   std::vector<int> order;
@@ -573,18 +580,7 @@ md_status upload_tables(Engine *e) {
       e->run_seats += r->g.ntiles;
       e->run_most = std::max(e->run_most, r->g.ntiles);
     }
-    if (e->run_seats > e->run_rep_cap) {
-      e->dfree(e->d_run_rep);
-      e->run_rep_cap = std::max(e->run_seats, 2 * e->run_rep_cap);
-      e->d_run_rep = (int32_t *)e->dmalloc((size_t)e->run_rep_cap * 4);
-      if (!e->d_run_rep) {
-        e->run_rep_cap = 0;
-        return MD_ERR_OOM;
-      }
-      // the captured graphs hold the table pointers in their kernel arguments
-      for (auto &kv : e->graphs) (void)hipGraphExecDestroy(kv.second);
-      e->graphs.clear();
-    }
+    if (!grow_table(e, &e->d_run_rep, &e->run_rep_cap, e->run_seats)) return MD_ERR_OOM;
   }
   const size_t need = 8 + (size_t)nt + (size_t)nct + (size_t)e->run_seats;
   if (need > e->h_tab_cap) {
