@@ -189,7 +189,7 @@ enum { ORDER_PASSES = 0, ORDER_SLABS = 1 };
 constexpr size_t WALK_BYTES = 16 * 64 * 4;  // Tables::walk
 // Tables::run: RUN_HEAD lines of 256 bytes (a batch's seats handed out, its
 // workgroups through), then RUN_LINES for each slot
-constexpr int RUN_HEAD = 2, RUN_LINES = 37;
+constexpr int RUN_HEAD = 2, RUN_LINES = 35;
 constexpr int RUN_SLOTS = 1024;  // a batch with more slots steps in two launches
 
 // Each replica has two descriptors (see SlotDev); CtlDev::var_ring says
@@ -206,6 +206,7 @@ struct Tables {
   int32_t *walk;
   int32_t *run;               // k_run's roll call and barriers (zero between launches)
   const int32_t *run_rep;     // a batch's seat in k_run -> replica
+  int32_t run_max;            // most workgroups that k_run's roll call admits
   int32_t nslots;
 };
 

@@ -49,7 +49,8 @@ namespace {
 constexpr int MIN_DEFAULT_MCAP = 48;
 constexpr int MIN_DEFAULT_HCAP = 16;
 constexpr int GRAPH_CHUNK = 64;      // steps per replay graph (largest)
-constexpr int RUN_STEPS = 256;       // steps per launch of k_run
+constexpr int RUN_STEPS = 256;       // steps per launch of k_run,
+constexpr int RUN_STEPS_FULL = 64;   // of a system that fills the chip (run_steps)
 constexpr int PROFILE_SETS = 2;      // ping-pong event sets when profiling
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -188,6 +189,12 @@ struct Replica {
 
 }  // namespace
 
+int run_limit() {
+  const char *v = getenv("MD_RUN_WORKGROUPS");
+  const int n = v ? atoi(v) : 0;
+  return n > 0 ? n : INT32_MAX;
+}
+
 struct Engine {
   hipStream_t user = nullptr;
   hipStream_t work = nullptr;
@@ -227,6 +234,9 @@ struct Engine {
   std::map<int, hipGraphExec_t> graphs;
   bool sticky_hip = false;
   bool verbose = getenv("MD_VERBOSE") != nullptr;
+  // MD_RUN_WORKGROUPS: at most so many workgroups take part in a launch of
+  // k_run (the others leave, as when they find no room)
+  int run_max = run_limit();
   size_t budget = 0, used = 0;
   int steps_per_run = GRAPH_CHUNK;
   int64_t host_target = 0;      // single system: target of the last md_step
@@ -254,6 +264,7 @@ struct Engine {
     t.walk = d_walk;
     t.run = d_run;
     t.run_rep = d_run_rep;
+    t.run_max = run_max;
     t.nslots = max_slots;
     return t;
   }
@@ -1027,14 +1038,19 @@ md_status replay(Engine *e, int k) {
 }
 
 // Advance a single system from absolute step `from` to `to` in launches of
-// up to steps_per_run steps (k_run), or in replays of steps_per_run steps and
-// a halving decomposition of the rest.
+// many steps (k_run), or in replays of steps_per_run steps and a halving
+// decomposition of the rest.  A system with more than two tiles per CU leaves
+// no room beside it: what else wants the chip waits for its launch to end, at
+// N = 256 000 up to 1.6 ms for 64 steps (8.5 for 256); a launch of its own
+// costs 18 us there, 1 % of its steps.
 md_status run_steps(Engine *e, int64_t from, int64_t to) {
   int64_t pos = from;
   if (use_run(e)) {
     const Tables T = e->tables();
+    const int full = e->rep[0]->g.ntiles > 2 * e->cus ? RUN_STEPS_FULL : RUN_STEPS;
+    const int most = e->trace ? std::min(full, MAX_REPLAY) : full;
     while (pos < to) {
-      const int k = (int)std::min<int64_t>(e->trace ? MAX_REPLAY : RUN_STEPS, to - pos);
+      const int k = (int)std::min<int64_t>(most, to - pos);
       const hipError_t err = launch_run(T, run_grid(e), k, to, !e->trace, 0, e->prec,
                                         e->accum || e->trace, e->mix, e->work);
       if (err != hipSuccess) return e->fail("run launch", err);
@@ -2148,9 +2164,13 @@ md_status md_batch_run(md_batch *b) {
     const Tables T = e->tables();
     for (int p : {PREC_FP32, PREC_FP64}) {
       if (!(e->prec & p)) continue;
-      const hipError_t err = launch_run(T, std::min(e->run_seats, run_capacity_of(e, p)),
-                                        e->steps_per_run, -1, !e->trace, e->run_seats, p, e->trace,
-                                        e->mix, e->work);
+      // (more seats than places: workgroups to spare, see k_run; with fewer they
+      // would only be dealt to the CUs unevenly: 8 replicas, 512 steps, 10 484 us
+      // instead of 9 154)
+      const int places = run_capacity_of(e, p);
+      const int grid = e->run_seats + (e->run_seats > places ? places : 0);
+      const hipError_t err = launch_run(T, grid, e->steps_per_run, -1, !e->trace, e->run_seats, p,
+                                        e->trace, e->mix, e->work);
       if (err != hipSuccess) return e->fail("run launch", err);
     }
     if (e->trace) {

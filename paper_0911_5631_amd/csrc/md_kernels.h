@@ -21,8 +21,9 @@ void launch_step(const Tables &T, int grid, int step_in_replay, int mode, int fo
 // Several steps of every replica of T in one launch (k_run): the first half
 // kick where the state is clean, then up to `steps` steps towards target (< 0:
 // each replica's own), and the step counters when commit is set.  grid: for a
-// system alone 8 ceil(tiles / 8); for a batch the workgroups that take its
-// `seats`; at most run_capacity() (workgroups of the kernel resident at once).
+// system alone (seats 0) 8 ceil(tiles / 8); for a batch its `seats` or more.  A system
+// must not have more than run_capacity() (workgroups of the kernel resident at
+// once).
 hipError_t launch_run(const Tables &T, int grid, int steps, long long target, bool commit,
                       int seats, int precision, bool accum, bool mix, hipStream_t s);
 int run_capacity(int precision, bool accum, bool mix, int cus);

@@ -1776,6 +1776,14 @@ __device__ __forceinline__ bool unordered(SlotC &S, const Ctl &C, int64_t k, int
 // ld).
 // unord(): whether the atoms are not in cell order (asked again where needed
 // instead of held).  si: index of the step in the replay.
+// A counter of arrivals at barriers of k_run carries this bit once one of the
+// workgroups that count there has latched an error; set before the workgroup's
+// next arrival.
+constexpr int RUN_BAD = 1 << 29;
+__device__ __forceinline__ void bring_error(int32_t *counter) {
+  __hip_atomic_fetch_or(counter, RUN_BAD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <bool MIX>
 struct StepLds {
   // 4 slots of padding: a group of candidates may read up to 3 slots past the
@@ -1787,7 +1795,7 @@ struct StepLds {
   int8_t ssp[MIX ? WCAP + 4 : 1];
   unsigned long long sv[4];
   double sh[4][8];
-  int bad;  // k_run: this workgroup has latched an error
+  int32_t *call;  // k_run: this workgroup's counter of arrivals at barriers
 };
 // The end of a tile's step: (d), (e) and the next (a) -- x and v become those
 // of the next step -- the binning of r(k+1) where bin_next, the clearing of
@@ -1827,7 +1835,7 @@ __device__ __forceinline__ void finish_tile(SlotC &S, CtlDev &C, Lds &lds, int l
         const int bad =
             bin_next ? bin_atom<COH>(S, C, (int)mod3(k + 1), i, xn[0], xn[1], xn[2], k + 1)
                      : check_atom(S, C, xn[0], xn[1], xn[2], k + 1);
-        if (COH && bad) lds.bad = 1;
+        if (COH && bad) bring_error(lds.call);
       }
       if (put_v)
         for (int q = 0; q < 3; ++q) {
@@ -2504,8 +2512,9 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 // what else the GPU does is not known here (another stream, another process).
 // So each launch begins with a roll call: a workgroup counts itself in, and
 // the launch is committed to the workgroups present, to all of them once the
-// last has come, or to those that have come when one has waited ROLL_TICKS.
-// The others find the launch committed without them and leave.  Everybody
+// last has come, or to those that have come when one has waited long enough
+// (roll_wait).  The others find the launch committed without them and leave.
+// Everybody
 // who takes part is running and stays so, so every barrier completes, and
 // with fewer participants than tiles each steps several.  (The spin bound of
 // the barriers is a backstop: it latches ERR_STALL, and none of the launch's
@@ -2519,16 +2528,49 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 // only touched by its own workgroup.  (Plain stores with one write-back per
 // XCD, by the last workgroup to arrive there, missed stores of other waves
 // once in some 10^5 rebuilds.)
-constexpr long long ROLL_TICKS = 10000;  // 100 us of the 100 MHz clock
-// in a batch a replica's last workgroup may come when another's replica is
-// through: 64 steps of 13-60 us
-constexpr long long ROLL_TICKS_BATCH = 500000;  // 5 ms
+//
+// The longest wait for the others, in ticks of the 100 MHz clock, where `here`
+// of `size` have come for `steps` steps.  A system alone waits half as long as
+// the launch would lose by going on with those (a step is 12 us or more and
+// takes size / here times as long), and 50 us, as long as the workgroups take
+// to be dispatched: what fills the chip now is mostly another such launch, and
+// when that ends the rest come.  With a wait of 100 us for whoever had come,
+// and launches of 256 steps, the second of two systems of 256 000 atoms on two
+// streams went on with the 24 workgroups that found room: 1 000 steps each
+// took 131 and 31 ms, 600 steps of three systems up to 995 ms; now 46 and 47,
+// and 28 to 43 (in launches of a step 47 and 47, and 47).
+// In a batch a replica's last workgroup may come when another's replica is
+// through, 64 steps of 13-60 us.
+constexpr long long ROLL_TICKS = 5000, ROLL_TICKS_BATCH = 500000, ROLL_TICKS_STEP = 600;
+__device__ __forceinline__ bool roll_wait(long long waited, int here, int size, int steps,
+                                          bool solo) {
+  return waited * here <
+         size * (solo ? ROLL_TICKS : ROLL_TICKS_BATCH) + (long long)(size - here) * steps * ROLL_TICKS_STEP;
+}
 constexpr int RUN_SPINS = 1 << 22;
-// A replica's words of Tables::run, each on its own 256-byte line; zero between
-// launches.
-enum { RUN_GROUPS = 32, RUN_ROOT = 32, RUN_EPOCH = 33, RUN_ARRIVE = 34, RUN_STATE = 35,
-       RUN_EXIT = 36, RUN_END = 37 };
+// A replica's lines of Tables::run, 256 bytes each; zero between launches.
+// Whatever all workgroups count is counted in 32 groups, then over the groups:
+// 1 000 workgroups on one counter take 12.7 us, in 32 groups 2.0.  A group's
+// line and the root's hold the words RUN_BAR (arrivals at barriers), RUN_CALL
+// (at the roll call; ROLL_CLOSED: it is over), RUN_GONE (workgroups through)
+// and RUN_BASE (rank of the group's first, of a roll call that was closed).
+enum { RUN_GROUPS = 32, RUN_ROOT = 32, RUN_EPOCH = 33, RUN_STATE = 34, RUN_END = 35 };
+enum { RUN_BAR = 0, RUN_CALL = 1, RUN_GONE = 2, RUN_BASE = 3, RUN_WORDS = 4 };
 static_assert(RUN_END <= RUN_LINES, "Tables::run");
+constexpr int ROLL_CLOSED = 1 << 30;
+// Member q of n counts itself at a word of its group (`word` of its line):
+// true for the last of all.
+__device__ __forceinline__ int group_size(int g, int n) {
+  return (n - g + RUN_GROUPS - 1) / RUN_GROUPS;
+}
+__device__ __forceinline__ bool count_in(int32_t *w, int word, int q, int n, int *index) {
+  constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
+  const int g = q & (RUN_GROUPS - 1);
+  *index = __hip_atomic_fetch_add(&w[64 * g + word], 1, __ATOMIC_RELAXED, AG);
+  return *index == group_size(g, n) - 1 &&
+         __hip_atomic_fetch_add(&w[64 * RUN_ROOT + word], 1, __ATOMIC_RELAXED, AG) ==
+             min(n, (int)RUN_GROUPS) - 1;
+}
 
 // A participant's place among n (epoch: barriers passed).
 struct RunSeat {
@@ -2541,49 +2583,56 @@ struct RunOut {
   unsigned long long vbits;
   int stop;
 };
-// A counter of arrivals also counts, from this bit on, those that bring an
-// error (a launch's arrivals at one counter stay below it: 32 workgroups of a
-// group times some 800 barriers); the epoch word carries RUN_STOP.
-constexpr int RUN_BAD = 1 << 20, RUN_STOP = 1 << 30;
+// In the epoch word: the run stops at this barrier.
+constexpr int RUN_STOP = 1 << 30;
 // The epoch word once it has reached epoch v, or -1.
 __device__ __forceinline__ int run_wait(int32_t *f, int v) {
+#pragma unroll 1
   for (int it = 0; it < RUN_SPINS; ++it) {
-    const int e = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int e = __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     if ((e & (RUN_STOP - 1)) >= v) return e;
     __builtin_amdgcn_s_sleep(1);
   }
   return -1;
 }
 
-// The grid barrier.  Arrivals are counted in 32 groups, then over the groups:
-// 1 000 workgroups on one counter took 12.7 us, in 32 groups 2.0.
+// The grid barrier.
 // drop: plain loads after it see what was stored (device-scope) before it:
 // the caches of the CU and of its XCD are invalidated, by one wave for its
 // workgroup.
 // ring: the maximum speed of that ring entry (< 0: none) is left in `out`,
 // read by one wave.
 // Whether the run stops is one decision for all: it goes with the epoch, from
-// what every workgroup brought (`bad`).  (The error word itself may already
-// hold an error of the next phase, which a workgroup that was quicker is in:
-// one that acted on it would leave the others waiting.)  A workgroup whose
-// barrier gives up stops, and brings that to the next one it comes to.
+// what every workgroup brought (bring_error).  (The error word itself may
+// already hold an error of the next phase, which a workgroup that was quicker
+// is in: one that acted on it would leave the others waiting.)  A workgroup
+// whose barrier gives up stops, and brings that to the next one it comes to.
 __device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, int ring, SlotC &S0, CtlDev &C,
-                                            int &bad, RunOut &out) {
+                                            RunOut &out) {
   constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
-  int32_t *w = p.w;
   __builtin_amdgcn_s_waitcnt(0);  // this wave's device-scope stores have arrived
   __syncthreads();
   ++p.epoch;
   if (threadIdx.x < 64) {
     int e = 0;
     if (threadIdx.x == 0) {
-      const int g = p.rank & (RUN_GROUPS - 1), in = (p.n - g + RUN_GROUPS - 1) / RUN_GROUPS;
+      // (both worked out here: left to itself the compiler holds them across
+      // the step, spilled, and the reloads are in the barrier's chain)
+      auto wg = gp(p.w);
+      int one;
+      asm volatile("v_mov_b32 %0, 1" : "=v"(one));
+      asm volatile("" : "+v"(wg));
+      int32_t *w = (int32_t *)wg;
+      const int g = p.rank & (RUN_GROUPS - 1), in = group_size(g, p.n);
       const int ng = p.n < RUN_GROUPS ? p.n : RUN_GROUPS;
-      const int mine = bad ? RUN_BAD + 1 : 1;
-      const int got = __hip_atomic_fetch_add(&w[64 * g], mine, __ATOMIC_RELAXED, AG) + mine;
+      const int got = __hip_atomic_fetch_add(&w[64 * g], one, __ATOMIC_RELAXED, AG) + 1;
       if ((got & (RUN_BAD - 1)) == p.epoch * in) {
-        const int ours = got >= RUN_BAD ? RUN_BAD + 1 : 1;
-        const int all = __hip_atomic_fetch_add(&w[64 * RUN_ROOT], ours, __ATOMIC_RELAXED, AG) + ours;
+        if (got >= RUN_BAD) {
+          bring_error(&w[64 * RUN_ROOT]);
+          __builtin_amdgcn_s_waitcnt(0);  // before the arrival below
+        }
+        const int all = __hip_atomic_fetch_add(&w[64 * RUN_ROOT], one, __ATOMIC_RELAXED, AG) + 1;
         if ((all & (RUN_BAD - 1)) == p.epoch * ng)
           __hip_atomic_store(&w[64 * RUN_EPOCH], p.epoch | (all >= RUN_BAD ? RUN_STOP : 0),
                              __ATOMIC_RELAXED, AG);
@@ -2591,7 +2640,7 @@ __device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, int ring, Slo
       e = run_wait(&w[64 * RUN_EPOCH], p.epoch);
       if (e < 0) {
         latch_error(C, ERR_STALL, C.done + 1);
-        bad = 1;
+        bring_error(&w[64 * g]);
       }
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -2607,6 +2656,32 @@ __device__ __forceinline__ void run_barrier(RunSeat &p, bool drop, int ring, Slo
     }
   }
   __syncthreads();
+}
+
+// The roll call's result, once: all `size` (everybody has come), or those that
+// have come when it is closed, at most `limit`.  A workgroup counts itself in
+// its group before the group is closed, or finds it closed.
+__device__ __forceinline__ void roll_close(int32_t *w, int size, int limit, int all) {
+  constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
+  int zero = 0;
+  const int claim = all <= limit && all > 0 ? all : -1;
+  if (!__hip_atomic_compare_exchange_strong(&w[64 * RUN_STATE], &zero, claim, __ATOMIC_RELAXED,
+                                            __ATOMIC_RELAXED, AG) || claim > 0)
+    return;
+  int n = 0;
+  for (int g = 0; g < min(size, (int)RUN_GROUPS); ++g) {
+    __hip_atomic_store(&w[64 * g + RUN_BASE], n, __ATOMIC_RELAXED, AG);
+    n += __hip_atomic_fetch_or(&w[64 * g + RUN_CALL], ROLL_CLOSED, __ATOMIC_RELAXED, AG);
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // the bases have arrived
+  __hip_atomic_store(&w[64 * RUN_STATE], min(n, limit), __ATOMIC_RELAXED, AG);
+}
+__device__ __forceinline__ int roll_here(const int32_t *w, int size) {
+  int n = 0;
+  for (int g = 0; g < min(size, (int)RUN_GROUPS); ++g)
+    n += __hip_atomic_load(&w[64 * g + RUN_CALL], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+         (ROLL_CLOSED - 1);
+  return n;
 }
 
 // One workgroup's part in steps done + 1 .. min(done + steps, target) of
@@ -2646,40 +2721,42 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
   // (read here, every word: a workgroup that comes after the others have gone
   // on may find other words, and takes no part)
   asm volatile("" ::"s"(done), "s"(target), "s"(reo1), "s"(var), "s"((int)ord), "s"((int)clean),
-               "s"((int)ahead), "s"(bins_step), "s"((int)idle), "s"(force_step),
-               "s"(__double_as_longlong(D2)));
+               "s"((int)ahead), "s"((int)idle), "s"(__double_as_longlong(D2)));
   // roll call
   RunSeat me;
   me.w = w;
   me.epoch = 0;
   if (threadIdx.x == 0) {
-    const int rank = __hip_atomic_fetch_add(&w[64 * RUN_ARRIVE], 1, __ATOMIC_RELAXED, AG);
-    int n = 0, zero = 0;
-    if (rank == size - 1)
-      __hip_atomic_compare_exchange_strong(&w[64 * RUN_STATE], &zero, rank + 1, __ATOMIC_RELAXED,
-                                           __ATOMIC_RELAXED, AG);
+    int index;
+    if (count_in(w, RUN_CALL, seat, size, &index)) roll_close(w, size, T.run_max, size);
+    int n = 0;
     const long long t0 = (long long)__builtin_amdgcn_s_memrealtime();
-    while ((n = __hip_atomic_load(&w[64 * RUN_STATE], __ATOMIC_RELAXED, AG)) == 0) {
-      if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > (solo ? ROLL_TICKS : ROLL_TICKS_BATCH)) {
-        zero = 0;
-        __hip_atomic_compare_exchange_strong(
-            &w[64 * RUN_STATE], &zero,
-            __hip_atomic_load(&w[64 * RUN_ARRIVE], __ATOMIC_RELAXED, AG), __ATOMIC_RELAXED,
-            __ATOMIC_RELAXED, AG);
+    while ((n = __hip_atomic_load(&w[64 * RUN_STATE], __ATOMIC_RELAXED, AG)) <= 0) {
+      // (the first of a group looks after the others)
+      const long long t = (long long)__builtin_amdgcn_s_memrealtime() - t0;
+      if (n == 0 && index == 0 && t >= (solo ? ROLL_TICKS : ROLL_TICKS_BATCH)) {
+        const int here = roll_here(w, size);
+        if (!roll_wait(t, here, size, idle ? 0 : (int)(end - done), solo))
+          roll_close(w, size, T.run_max, 0);
       }
       __builtin_amdgcn_s_sleep(1);
     }
-    s_rank = rank;
+    // (the workgroups of a roll call that was closed are numbered by their
+    // groups; one that came later takes no part)
+    s_rank = n == size ? seat
+             : (index & ROLL_CLOSED) != 0
+                 ? size
+                 : __hip_atomic_load(&w[64 * (seat & (RUN_GROUPS - 1)) + RUN_BASE],
+                                     __ATOMIC_RELAXED, AG) + index;
     s_n = n;
-    lds.bad = 0;
+    lds.call = &w[64 * (s_rank & (RUN_GROUPS - 1)) + RUN_BAR];
   }
   __syncthreads();
   const int n = __builtin_amdgcn_readfirstlane(s_n);
   const bool all = n == size;
   // with everybody present a workgroup's place goes by its number, so that
-  // each XCD has a contiguous eighth of the tiles of a system that is alone;
-  // else by its arrival
-  const int rank = all ? seat : __builtin_amdgcn_readfirstlane(s_rank);
+  // each XCD has a contiguous eighth of the tiles of a system that is alone
+  const int rank = __builtin_amdgcn_readfirstlane(s_rank);
   if (rank < n) {
     me.rank = rank;
     me.n = n;
@@ -2696,7 +2773,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     const bool lead = rank == 0 && threadIdx.x == 0;
     int stop = idle ? 1 : 0;  // nothing to do: the loop below is not entered
     auto barrier = [&](bool drop, bool ring) {
-      run_barrier(me, drop, ring ? (int)mod3(k) : -1, S0, C, lds.bad, out);
+      run_barrier(me, drop, ring ? (int)mod3(k) : -1, S0, C, out);
       stop = __builtin_amdgcn_readfirstlane(out.stop);
     };
     if (lead) {
@@ -2714,7 +2791,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     int dirty = 7;  // cell-layer sets to be cleared (as far as is known)
     if (clean && !idle) {
       for (int t = first; t < tend; t += tstep)
-        if (kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned)) lds.bad = 1;
+        if (kick_tile<true>(slot(T, 2 * r + var), C, t, done, binned)) bring_error(lds.call);
       barrier(false, false);
     }
     // the decisions of k_sort for step k
@@ -2807,7 +2884,7 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
           if (i < S.n && bin_atom<true>(S, C, set, i, ld<true>(&gp((const double *)S.P[pb][0])[i]),
                                         ld<true>(&gp((const double *)S.P[pb][1])[i]),
                                         ld<true>(&gp((const double *)S.P[pb][2])[i]), k))
-            lds.bad = 1;
+            bring_error(lds.call);
         }
         // (counted where binning ahead would have missed it)
         if (lead && !uniform(bins_rule(S0, force_step, k, D2, V2))) C.late_bins += 1;
@@ -2845,45 +2922,43 @@ __device__ __forceinline__ void run_replica(const Tables &T, StepLds<MIX> &lds, 
     }
   }
   // the last to leave clears the words for the next launch
-  if (threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(&w[64 * RUN_EXIT], 1, __ATOMIC_RELAXED, AG) == size - 1)
-    for (int q = 0; q < RUN_LINES; ++q)
-      __hip_atomic_store(&w[64 * q], 0, __ATOMIC_RELAXED, AG);
+  int index;
+  if (threadIdx.x == 0 && count_in(w, RUN_GONE, seat, size, &index))
+    for (int q = 0; q < RUN_END; ++q)
+      for (int u = 0; u < RUN_WORDS; u += 2)
+        __hip_atomic_store((unsigned long long *)&w[64 * q + u], 0ull, __ATOMIC_RELAXED, AG);
 }
 
-// A system alone: one workgroup per tile.  A batch: the workgroups take the
-// seats of its replicas (seats of them in all, SlotDev::run_n each) in order;
-// one whose replica is through takes the next, so every replica goes through
-// its steps at its own pace, and none waits for another's rebuild.  Seats are
-// handed out in order and a replica's are never more than the launch has
-// workgroups, so the first replica that is not through always gets all of
-// its workgroups, or goes on with those that have come when it has waited
-// long enough.
+// A system alone: one workgroup per tile.  A batch: a workgroup takes the next
+// of the seats of its replicas (SlotDev::run_n each, one after the other) and
+// ends with it, so every replica goes through its steps at its own pace, none
+// waits for another's rebuild, and the chip is shared with other streams at
+// every seat's end (with 1 024 workgroups that went from seat to seat, another
+// stream's kernel waited 16 ms beside 256 replicas).  The launch has more
+// workgroups than seats, since each XCD is dealt an eighth of them, and one
+// that is through with its seats sooner takes more.  Seats are handed out in order and a replica's are
+// never more than the chip holds at once, so the first replica that is not
+// through gets all of its workgroups as the chip empties, or goes on with
+// those that have come when it has waited long enough.
 template <typename R, bool ACC, bool MIX>
 __global__ __launch_bounds__(TILE, MIX ? 3 : 4) void k_run(Tables T, int steps, long long target,
                                                          int commit, int seats) {
   constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
   __shared__ StepLds<MIX> lds;
   const bool solo = seats == 0;  // a system alone: its workgroups are its seats
-  int &s_seat = ((int *)lds.sv)[2];
-  for (bool more = true; more; more = !solo) {
-    int q = blockIdx.x, r = 0;
-    if (!solo) {
-      __syncthreads();
-      if (threadIdx.x == 0)
-        s_seat = __hip_atomic_fetch_add(&T.run[0], 1, __ATOMIC_RELAXED, AG);
-      __syncthreads();
-      q = __builtin_amdgcn_readfirstlane(s_seat);
-      if (q >= seats) break;
-      r = cview(T.run_rep)[q];
-    }
-    SlotC &S0 = slot(T, 2 * r);
-    if (S0.fp64 != (sizeof(R) == 8)) continue;
+  int q = blockIdx.x, r = 0;
+  if (!solo) {
+    int &s_seat = ((int *)lds.sv)[2];
+    if (threadIdx.x == 0) s_seat = __hip_atomic_fetch_add(&T.run[0], 1, __ATOMIC_RELAXED, AG);
+    __syncthreads();
+    q = __builtin_amdgcn_readfirstlane(s_seat);
+    r = q < seats ? cview(T.run_rep)[q] : -1;
+  }
+  SlotC &S0 = slot(T, 2 * max(r, 0));
+  if (r >= 0 && S0.fp64 == (sizeof(R) == 8))
     run_replica<R, ACC, MIX>(T, lds, r, solo ? q : q - S0.run_off, solo ? (int)gridDim.x : S0.run_n,
                              solo, steps, target, commit);
-  }
-  if (solo) return;
-  if (threadIdx.x == 0 &&
+  if (!solo && threadIdx.x == 0 &&
       __hip_atomic_fetch_add(&T.run[64], 1, __ATOMIC_RELAXED, AG) == (int)gridDim.x - 1) {
     __hip_atomic_store(&T.run[0], 0, __ATOMIC_RELAXED, AG);
     __hip_atomic_store(&T.run[64], 0, __ATOMIC_RELAXED, AG);
