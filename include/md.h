@@ -178,10 +178,16 @@ typedef struct {
 
 /* Launch configuration (md_configure, md_batch_configure).  None of these
  * changes the arithmetic or its order, so a trajectory is the same bit for
- * bit under any of them; they only cut the same work differently.  In: 0
- * asks for the library's choice.  Out: the values in use. */
+ * bit under any of them, also when they change in the middle of a run; they
+ * only cut the same work differently.  In: 0 asks for the library's choice.
+ * With grid, sort_grid and sort_split all 0, a system whose tiles the chip
+ * holds at once (about 262 000 atoms), or a batch of such systems, takes many
+ * steps per launch; any of the three selects launches of their own for every
+ * step.  Out: the values in use, and 0 for those that many steps per launch do
+ * not use (a batch of larger systems also reports 0 for what was not asked). */
 typedef struct {
-    int32_t steps_per_run; /* steps per captured graph replay, 1..64 (0: 64) */
+    int32_t steps_per_run; /* steps per captured graph replay, in a batch per
+                              md_batch_run, 1..64 (0: 64) */
     int32_t grid;          /* workgroups per step-kernel launch, 1..65535 (0: a
                               single system one per 256-atom tile up to the
                               number resident at once, 4 per CU; a batch 2048) */

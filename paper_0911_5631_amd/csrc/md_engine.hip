@@ -1491,6 +1491,15 @@ md_status configure(Engine *e, md_launch_t *cfg) {
   cfg->sort_grid = e->cgrid;
   cfg->sort_split = e->split;
   cfg->tile_order = tile_order(e);
+  // what many steps per launch do not use stays 0, so that a configuration
+  // that was returned asks for the same again (a batch goes by its systems
+  // from run to run)
+  const bool asked = e->grid_req > 0 || e->cgrid_req > 0 || e->split_req > 0;
+  if (!asked && (e->batch || use_run(e))) {
+    cfg->grid = cfg->sort_grid = cfg->sort_split = 0;
+    cfg->tile_order = e->order_req;
+    if (!e->batch) cfg->steps_per_run = cfg->tile_order = 0;
+  }
   return MD_OK;
 }
 

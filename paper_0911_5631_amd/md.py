@@ -16,6 +16,7 @@ import numpy as np
 
 from . import _lib as L
 from ._lib import MDError, check, lib
+from .tune import BATCH_CANDIDATES
 
 RC_SOFT_SPHERE = 2.0 ** (1.0 / 6.0)
 
@@ -315,6 +316,8 @@ class System:
 
 class Batch:
     """Many independent systems advanced by the same kernel launches."""
+
+    launch_candidates = BATCH_CANDIDATES     # what tune.autotune tries
 
     def __init__(self, hbm_budget: int, max_slots: int, steps_per_run: int = 64, *,
                  allocator: str = "torch", stream=None):

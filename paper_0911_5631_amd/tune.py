@@ -13,6 +13,9 @@ every system's trajectory stays bit-identical whatever is chosen:
                  XCDs (passes of consecutive runs, or one slab of tiles per
                  XCD so that z-neighbour rows share an L2).
 
+With grid, sort_grid and sort_split all 0, systems that the chip holds at once
+take many steps per launch; the other knobs are of launches of one step.
+
 A batch is tuned on its own admitted mix with real runs (the steps count
 toward the systems' targets).  A trial is scored by the atom-steps the batch
 actually advanced per second, read from the device step counters before and
@@ -43,6 +46,12 @@ DEFAULT_CANDIDATES = (
     {"steps_per_run": 64, "grid": 2048, "sort_grid": 4096, "sort_split": 1, "tile_order": 1},
     {"steps_per_run": 64, "grid": 2048, "sort_grid": 2048, "sort_split": 2, "tile_order": 1},
 )
+
+# of a batch: many steps per launch first (steps_per_run is then the steps of a
+# launch), then launches of a step
+BATCH_CANDIDATES = tuple(
+    {"steps_per_run": k, "grid": 0, "sort_grid": 0, "sort_split": 0, "tile_order": 0}
+    for k in (64, 32, 16)) + DEFAULT_CANDIDATES
 
 SINGLE_CANDIDATES = (
     {"steps_per_run": 64, "grid": 0, "sort_grid": 0, "sort_split": 0, "tile_order": 2},
@@ -91,7 +100,7 @@ def store(path: Optional[str], key: str, entry: Dict) -> None:
     os.replace(tmp, path)
 
 
-def autotune(batch, candidates: Iterable[Mapping] = DEFAULT_CANDIDATES, runs: int = 2,
+def autotune(batch, candidates: Optional[Iterable[Mapping]] = None, runs: int = 2,
              cache_path: Optional[str] = None, key: Optional[str] = None,
              clock=None, warm_runs: int = 0, trial_steps: int = 0) -> Dict:
     """Time ``runs`` runs of ``batch`` per candidate (after one untimed run
@@ -105,8 +114,12 @@ def autotune(batch, candidates: Iterable[Mapping] = DEFAULT_CANDIDATES, runs: in
     are not scored over a window that happens to hold fewer rebuilds.
 
     ``batch`` offers configure(**knobs), run(), poll() (synchronises) and
-    progress() -> (atom-steps done, systems running, fewest steps left)."""
+    progress() -> (atom-steps done, systems running, fewest steps left); the
+    candidates, unless given, are its ``launch_candidates`` (those of launches
+    of a step if it names none)."""
     clock = clock or time.perf_counter
+    if candidates is None:
+        candidates = getattr(batch, "launch_candidates", DEFAULT_CANDIDATES)
     trials: List[Dict] = []
     _, running, left = batch.progress()
     for _ in range(warm_runs):
@@ -155,12 +168,19 @@ def autotune_system(system, n_atoms: int, candidates: Iterable[Mapping] = SINGLE
                     key: Optional[str] = None, clock=None) -> Dict:
     """The same for one system: each candidate advances it ``steps`` real
     steps (after one untimed replay that warms the new graphs), timed to the
-    synchronising props() call; the fastest is kept."""
+    synchronising props() call; the fastest is kept.  A candidate that comes to
+    the same configuration as an earlier one (knobs that the system's launches
+    do not use) is not timed again."""
     clock = clock or time.perf_counter
     trials: List[Dict] = []
+    seen = set()
     for cand in candidates:
         c = _cfg(cand)
-        system.configure(**c)
+        used = tuple(system.configure(**c).values())
+        if used in seen:
+            trials.append({**c, "skipped": "the same as an earlier candidate"})
+            continue
+        seen.add(used)
         system.step(c["steps_per_run"] or 64)
         system.props()
         t0 = clock()
@@ -168,7 +188,8 @@ def autotune_system(system, n_atoms: int, candidates: Iterable[Mapping] = SINGLE
         system.props()
         el = clock() - t0
         trials.append({**c, "atom_steps_per_s": n_atoms * steps / el if el > 0 else 0.0})
-    best = max(trials, key=lambda t: t["atom_steps_per_s"])
+    best = max((t for t in trials if "atom_steps_per_s" in t),
+               key=lambda t: t["atom_steps_per_s"])
     used = system.configure(**{k: best[k] for k in KNOBS})
     if key:
         store(cache_path, key, {"config": {k: best[k] for k in KNOBS},
