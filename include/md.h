@@ -231,7 +231,9 @@ md_status md_query_bytes(const md_params *p, size_t *bytes);
  * bin, sort into cell order, build the neighbour matrix (unless shell == 0),
  * forces, properties, and the first rebuild decision (accumulated
  * displacement = vmax*dt).  hip_stream: a hipStream_t, or NULL.  a:
- * allocator, or NULL for hipMalloc.  On success *out owns a new system.
+ * allocator, or NULL for hipMalloc.  On success *out owns a new system, and
+ * with it pinned host memory that states pass through: 72 bytes per atom,
+ * 32 MiB from 16 MiB on (a batch has one such buffer, for its largest system).
  * Sync. */
 md_status md_create(const md_params *p, const double *pos, const double *vel,
                     const md_allocator *a, void *hip_stream, md_system **out);
@@ -261,9 +263,13 @@ md_status md_forces(md_system *s);
 
 /* Advance n_steps leapfrog steps (a)-(e), rebuilding on the device whenever
  * the displacement rule fires.  A system of up to about 262 000 atoms takes
- * many steps per launch; a larger one, or one whose launches md_configure
- * gave grids or a sort split of their own, replays captured HIP graphs.  The
- * trajectory is the same bit for bit.  Async. */
+ * many steps per launch (64 above about 131 000 atoms, where it leaves no room
+ * for other work beside it, else 256); a larger one, or one whose launches
+ * md_configure gave grids or a sort split of their own, replays captured HIP
+ * graphs.  The trajectory is the same bit for bit.  Where other work holds the
+ * chip such a launch goes on with the workgroups that find room; for tests the
+ * environment variable MD_RUN_WORKGROUPS, read when a system or batch is
+ * created, limits their number.  Async. */
 md_status md_step(md_system *s, int64_t n_steps);
 
 /* Properties after the last completed step (or creation / md_forces).
@@ -418,19 +424,22 @@ md_status md_newton3_ab_noalloc(md_system *s, int32_t variant, int32_t reps, dou
 void md_destroy(md_system *s);
 
 /* ---------------------------------------------------------------------------
- * Batches: many independent systems advanced together.  Each kernel launch
- * of a batched step covers the tiles of every active system, so small
- * systems share the GPU; the per-system arithmetic is exactly that of an
- * md_system with the same parameters, so a system's trajectory is the same
- * bit for bit alone or in any mix.
+ * Batches: many independent systems advanced together.  A launch covers
+ * every active system, so small systems share the GPU: many steps of each at
+ * its own pace where the chip holds the tiles of every one of them at once,
+ * else (or with grids asked for, md_launch_t) the tiles of all of them for one
+ * step, replayed as HIP graphs.  The per-system arithmetic is exactly that of
+ * an md_system with the same parameters, so a system's trajectory is the same
+ * bit for bit alone or in any mix, also when the mix or the configuration
+ * changes while it runs.
  * ------------------------------------------------------------------------- */
 
 /* A batch with room for max_slots systems and hbm_budget bytes of their
- * device state; steps_per_run (1..64) steps are replayed per md_batch_run. */
+ * device state; steps_per_run (1..64) steps are taken per md_batch_run. */
 md_status md_batch_create(size_t hbm_budget, int32_t max_slots, int32_t steps_per_run,
                           const md_allocator *a, void *hip_stream, md_batch **out);
 
-/* Launch configuration of later runs (see md_launch_t): steps replayed per
+/* Launch configuration of later runs (see md_launch_t): steps per
  * md_batch_run and the workgroups of the launches.  *cfg gets the
  * configuration in use.  Used by the autotuner.  Sync. */
 md_status md_batch_configure(md_batch *b, md_launch_t *cfg);

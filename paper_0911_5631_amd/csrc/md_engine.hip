@@ -962,12 +962,13 @@ int run_grid(const Engine *e) { return (e->rep[0]->g.ntiles + 7) / 8 * 8; }
 // single system, or every replica of a batch, whose tiles are all resident at
 // once (1 024 tiles, 262 144 atoms; a mixture 768), unless its launches are
 // timed one by one or were given grids of their own.  At N = 256 000 (1 000
-// tiles) a step takes 24.7 us this way and 30.1 in two launches, at N = 864
-// 11.5 and 17.3; 48 replicas of 864 to 32 000 atoms 64 and 108, 2 of them 15
-// and 40 (in launches every step waits for the slowest tile of any replica
-// that rebuilds); 256 replicas, 12 rounds of seats, 277 and 284.  Beyond the
+// tiles) a step takes 23.2 us this way and 29.0 in two launches, at N = 864
+// 10.6 and 16.1; 48 replicas of 864 to 32 000 atoms 60 and 103, 2 of them 14
+// and 39 (in launches every step waits for the slowest tile of any replica
+// that rebuilds); 256 replicas, 12 rounds of seats, 265 and 270.  Beyond the
 // limit each workgroup would walk several tiles with device-scope reads,
-// where k_step's tiles share their neighbours through the XCD's L2.
+// where k_step's tiles share their neighbours through the XCD's L2.  A batch
+// may go from one to the other between two runs.
 int run_capacity_of(Engine *e, int prec) {
   const bool acc = e->accum || e->trace;
   int &cap = e->run_cap[prec == PREC_FP64][acc][e->mix];

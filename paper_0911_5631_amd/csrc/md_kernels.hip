@@ -1,6 +1,6 @@
 // md_kernels.hip -- gfx950 kernels of the soft-sphere MD hot path.
 //
-// One time step k of every replica of an engine is two launches:
+// A time step k of every replica of an engine is two launches:
 //   k_sort  (b) when the displacement rule fires (always with the plain cell
 //           method): wrap, and a stable counting sort of the atoms by cell
 //           (Secs. 3.4, 3.5) -- cell_start from the occupancy counts, ranks
@@ -11,14 +11,18 @@
 //           cells); (d), (e) second half kick, kinetic energy, maximum speed;
 //           (a) of the next step: half kick and drift, and the binning of the
 //           new positions into the next cell-layer set.
-// Nothing waits for other workgroups inside a launch: the rebuild decision of
-// step k is recomputed by every workgroup of k_sort from the maximum speed of
-// step k-1 (one atomicMax per workgroup into a spread ring slot) and the
-// displacement committed by step k-1, and committed for k_step by the
-// workgroup of the replica's first cell tile, so no device-scope fence or
+// Nothing waits for other workgroups inside these launches: the rebuild
+// decision of step k is recomputed by every workgroup of k_sort from the
+// maximum speed of step k-1 (one atomicMax per workgroup into a spread ring
+// slot) and the displacement committed by step k-1, and committed for k_step by
+// the workgroup of the replica's first cell tile, so no device-scope fence or
 // "last block" finalisation is needed (on gfx950 a device-scope release writes
-// back the whole L2).  Properties are reduced on demand (k_props) in a fixed
-// order.
+// back the whole L2).
+// Replicas whose tiles the chip holds at once take many steps per launch
+//   k_run   the same parts in one kernel, with barriers over the replica's
+//           workgroups between them.
+// Either leaves a replica so that the other can go on with it.  Properties are
+// reduced on demand (k_props) in a fixed order.
 //
 // Floating point: compiled with -ffp-contract=off, so every FP64 expression
 // rounds as written (no fused multiply-add); cell indices and neighbour
@@ -2498,7 +2502,7 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// several steps of a single system in one launch
+// several steps in one launch
 // ---------------------------------------------------------------------------
 // A system whose tiles all fit on the chip at once (1 024 of them, 262 144
 // atoms) spends most of a step between kernels: at N = 110 592 a step of two
@@ -2523,9 +2527,10 @@ __device__ __forceinline__ void end_run(CtlDev &C, int K, int64_t base, int64_t 
 // What is shared: everything that another workgroup may read in the same
 // launch is stored device-scope (st) and read so (ld), past the caches that
 // only one XCD or CU sees.  The exceptions are the packed positions and
-// cell_start, which a build reads again and again: they are read plainly,
-// behind a barrier that invalidates the caches.  A tile's list and window are
-// only touched by its own workgroup.  (Plain stores with one write-back per
+// cell_start, which a build reads again and again, and the cells that
+// make_window reads: they are read plainly, behind a barrier that invalidates
+// the caches.  A tile's list, window and sums are only touched by its own
+// workgroup, the same for the whole launch.  (Plain stores with one write-back per
 // XCD, by the last workgroup to arrive there, missed stores of other waves
 // once in some 10^5 rebuilds.)
 //

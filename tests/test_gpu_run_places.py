@@ -106,3 +106,49 @@ def test_error_in_a_partial_run(places, monkeypatch):
         out.append((L.lib().md_props(s._h, C.byref(p)), p.step, p.n_rebuilds))
         s.close()
     assert out[0] == out[1] and out[0][0] in (-6, -7) and 0 < out[0][1] < 200
+
+
+def test_systems_and_a_batch_at_once():
+    """From three threads on streams of their own, more tiles than the chip
+    holds: whichever launches find room, every result is that of a run alone."""
+    import threading
+
+    import torch
+    from paper_0911_5631_amd.md import Batch, System
+    big = [_fluid(40, 7), _fluid(36, 8)]                       # 1 000 and 729 tiles
+    small = I.replica_batch(n_replicas=24, k_lo=6, k_hi=20, steps=0, seed=3)
+
+    def system(start, stream):
+        s = System(*start, shell=0.4, stream=stream)
+        for n in (150, 150):
+            s.step(n)
+        out = (*s.get_state(), s.props())
+        s.close()
+        return [out]
+
+    def batch(stream):
+        b = Batch(1 << 33, 24, 64, stream=stream)
+        slots = [b.admit(q.pos, q.vel, q.box, 300, shell=q.shell) for q in small]
+        for _ in range(5):
+            b.run()
+        b.poll()
+        out = [(*b.get_state(s), b.props(s)) for s in slots]
+        b.close()
+        return out
+
+    jobs = [lambda st: system(big[0], st), lambda st: system(big[1], st), batch]
+    alone = [job(torch.cuda.Stream()) for job in jobs]
+    got = [None] * 3
+
+    def work(k):
+        torch.cuda.set_device(0)
+        got[k] = jobs[k](torch.cuda.Stream())
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for a, g in zip(alone, got):
+        for x, y in zip(a, g):
+            assert all(np.array_equal(p, q) for p, q in zip(x[:-2], y[:-2])) and x[-2:] == y[-2:]
