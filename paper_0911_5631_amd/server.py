@@ -1,8 +1,8 @@
 """Serving loop: requests arrive over time (a Poisson trace), are admitted into
 one batch while their device memory fits the HBM budget and a slot is free,
-advance together in graph replays (continuous batching: a finished system's
-slot and memory go to the next queued request between replays), and leave
-when their steps are done.
+advance together in runs of steps_per_run steps (continuous batching: a
+finished system's slot and memory go to the next queued request between
+runs), and leave when their steps are done.
 
 Reported per request: queueing delay (arrival -> admission) and latency
 (arrival -> completion); for the run: p50 / p99 latency, offered load,

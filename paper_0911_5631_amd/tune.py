@@ -3,8 +3,8 @@
 The knobs are the ones that change neither the arithmetic nor its order, so
 every system's trajectory stays bit-identical whatever is chosen:
 
-  steps_per_run  length of the captured replay graph (amortises the per-run
-                 kick and host round trip);
+  steps_per_run  steps per run of a batch, or length of the captured replay
+                 graph (amortises the per-run kick and host round trip);
   grid           workgroups per step-kernel launch (tiles beyond the grid are
                  taken in further passes of the same workgroups);
   sort_grid      workgroups per sort launch;
